@@ -116,16 +116,16 @@ def draw(rng):
     if kind == "shots":
         circuit = rng.choice(["7q", "17q", "17q_ghz", "49q", "81q"])
         top = {"7q": 30000, "17q": 20000, "17q_ghz": 1000, "49q": 2000, "81q": 100}[circuit]
-        n = _log_int(rng, 1, top)
         screened = circuit in ("49q", "81q")
-        subset = rng.random() < 0.5
+        n = _log_int(rng, 24 if screened else 4, top)
+        subset = rng.random() < 0.5 or n < 300      # few shots: of a fixed number of faults
         return dict(kind="shots", circuit=circuit, precision=rng.choice(["fp32", "fp64"]),
                     shots=24 * n + 64 if screened else n,
-                    w_max=rng.randint(1, 4) if subset and not screened else -1,
+                    w_max=rng.randint(2, 4) if subset and not screened else -1,
                     p=round(10 ** rng.uniform(-3.5, -2.8), 7),
                     survivors=n if screened else 0, prefix=rng.random() < 0.5)
     if kind == "camps":
-        n = _log_int(rng, 4, 200)
+        n = _log_int(rng, 24, 200)
         return dict(kind="camps", circuit=rng.choice(["17q", "49q_snake"]), precision="fp64",
                     shots=24 * n + 64, w_max=-1, p=round(10 ** rng.uniform(-3.5, -2.8), 7),
                     survivors=n, prefix=rng.random() < 0.8)
