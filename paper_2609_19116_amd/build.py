@@ -28,6 +28,7 @@ SOURCES = [
     CSRC / "host" / "camps.cpp",
     CSRC / "host" / "capi.cpp",
     CSRC / "kernels" / "mps.hip",
+    CSRC / "kernels" / "mps_fast.hip",
     CSRC / "kernels" / "prescreen.hip",
     CSRC / "kernels" / "sampler.hip",
     CSRC / "kernels" / "batch.hip",

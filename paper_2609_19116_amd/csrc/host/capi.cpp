@@ -474,6 +474,14 @@ static int enqueue_shots(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, 
                          const PrefixCk* pk, const int64_t* n_dev, double* surv,
                          const int64_t* perm_in);
 
+// Whether a circuit's shots take the matrix-core kernels.  Not those with
+// controlled-S or CCZ gates: they leave sets of more than two overlapping
+// vectors with equal singular values, whose basis after a factorisation, and
+// with it which later centre moves find overlaps (the records' n2q and flops),
+// follows the last bit of the rotations' order and rounding.  Their records
+// stay what the round-robin kernels compute.
+static bool fast_path(const msc_circuit* c) { return c->pair_spectra; }
+
 // The wavefront kernel's pass over the shots (slots of bond cap wave_chi,
 // one shot per wavefront, shots taken from a shared counter), then the shots
 // that outgrew their slots, from their start (no fork) in the workgroup
@@ -484,11 +492,14 @@ static int enqueue_wave(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, i
                         const uint8_t* pauli, const int64_t* shot_idx, msc_shot_result* out,
                         int ck_mode, const PrefixCk* pk, const int64_t* n_dev, double* surv) {
     const int precision = cfg.precision, cw = cfg.wave_chi;
+    const bool fast = fast_path(c) && cw <= kFastWaveBond;
     Layout L = make_layout(c->n, cw, 2 * cw);
     if (L.slot_elems >= (int64_t(1) << 31)) return set_error(MSC_E_INVALID, "slot above 2^31 elements");
     int64_t teams = cfg.n_slots > 0 ? cfg.n_slots
                                     : static_cast<int64_t>(ctx->n_cu) *
-                                          mps_wave_blocks_per_cu(precision) * kWaveTeams;
+                                          (fast ? mps_fast_wave_blocks_per_cu(precision)
+                                                : mps_wave_blocks_per_cu(precision)) *
+                                          kWaveTeams;
     teams = std::max<int64_t>(1, std::min<int64_t>(teams, n));
     const int grid = static_cast<int>((teams + kWaveTeams - 1) / kWaveTeams);
     const int64_t slots = static_cast<int64_t>(grid) * kWaveTeams;
@@ -532,7 +543,8 @@ static int enqueue_wave(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, i
     MSC_HIP(launch_order(n, n_dev, off, shot_idx, n_csr, chan,
                          a.ck_mode == 2 ? c->n_channels : 0, static_cast<int64_t*>(dperm), otmp,
                          ctx->stream));
-    MSC_HIP(launch_mps_wave(precision, a, grid, ctx->stream));
+    MSC_HIP(fast ? launch_mps_fast_wave(precision, a, grid, ctx->stream)
+                 : launch_mps_wave(precision, a, grid, ctx->stream));
     int32_t n_retry = 0;
     MSC_HIP(hipMemcpyAsync(&n_retry, a.retry_count, sizeof(n_retry), hipMemcpyDeviceToHost,
                            ctx->stream));

@@ -334,6 +334,7 @@ int compile_circuit(msc_circuit* c) {
     std::vector<IrOp> ir;
     ir.reserve(c->ir.size());
     for (const auto& o : c->ir) {
+        if (o.kind == IR_G3 || (o.kind == IR_G2 && (o.g == G2_CS || o.g == G2_CSDG))) c->pair_spectra = false;
         if (o.kind == IR_G3) expand_ccz(o, ir);
         else ir.push_back(o);
     }

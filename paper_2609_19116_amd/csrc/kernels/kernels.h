@@ -139,6 +139,11 @@ int mps_blocks_per_cu(int precision, bool small);
 hipError_t launch_mps_wave(int precision, const MpsArgs& a, int grid, hipStream_t s);
 int mps_wave_blocks_per_cu(int precision);
 constexpr int kWaveTeams = 4;      // shots per workgroup of the wavefront kernel
+// The same on the matrix cores (mps_fast.hip), for slots of bond cap at most
+// kFastWaveBond.
+constexpr int kFastWaveBond = 16;
+hipError_t launch_mps_fast_wave(int precision, const MpsArgs& a, int grid, hipStream_t s);
+int mps_fast_wave_blocks_per_cu(int precision);
 
 // Bits of the CSR check flag written by the screen and validation kernels
 enum CsrFlag : int {

@@ -120,6 +120,7 @@ struct msc_circuit {
     std::vector<msc::DevOp> ops;
     int64_t n_twosite = 0, n_swaps = 0, n_product_swaps = 0, n_moves = 0;
     int final_site = 0;
+    bool pair_spectra = true;            // no controlled-S and no CCZ gate
     std::vector<int32_t> chan_op;        // op index of each channel's OP_FAULT
     // expected outcomes
     std::vector<uint8_t> expected;
