@@ -370,6 +370,7 @@ struct RunCfg {
     int lds_width = 32;
     int park_side = 0;           // 0: the shot kernel does every update
     int wave_chi = 0;            // > 0: one shot per wavefront in slots of this bond cap
+    bool fast_wide = false;      // slots of a cap above 16 chosen for the matrix-core kernels
     bool graphs = false;
     LxTiles tiles[kLxBuckets];
 };
@@ -492,17 +493,18 @@ static int enqueue_wave(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, i
                         const uint8_t* pauli, const int64_t* shot_idx, msc_shot_result* out,
                         int ck_mode, const PrefixCk* pk, const int64_t* n_dev, double* surv) {
     const int precision = cfg.precision, cw = cfg.wave_chi;
-    const bool fast = fast_path(c) && cw <= kFastWaveBond;
+    const bool fast = fast_path(c) && (cw <= kFastWaveBond || cfg.fast_wide);
+    const FastKernel fk = fast_kernel(cw);
+    const int per_wg = fast ? fk.teams : kWaveTeams;
     Layout L = make_layout(c->n, cw, 2 * cw);
     if (L.slot_elems >= (int64_t(1) << 31)) return set_error(MSC_E_INVALID, "slot above 2^31 elements");
-    int64_t teams = cfg.n_slots > 0 ? cfg.n_slots
-                                    : static_cast<int64_t>(ctx->n_cu) *
-                                          (fast ? mps_fast_wave_blocks_per_cu(precision)
-                                                : mps_wave_blocks_per_cu(precision)) *
-                                          kWaveTeams;
+    int64_t teams = cfg.n_slots;
+    if (teams <= 0)
+        teams = static_cast<int64_t>(ctx->n_cu) * per_wg *
+                (fast ? fk.blocks_per_cu : mps_wave_blocks_per_cu(precision));
     teams = std::max<int64_t>(1, std::min<int64_t>(teams, n));
-    const int grid = static_cast<int>((teams + kWaveTeams - 1) / kWaveTeams);
-    const int64_t slots = static_cast<int64_t>(grid) * kWaveTeams;
+    const int grid = static_cast<int>((teams + per_wg - 1) / per_wg);
+    const int64_t slots = static_cast<int64_t>(grid) * per_wg;
     const size_t tsize = precision == MSC_FP64 ? sizeof(double) : sizeof(float);
     void *arena, *scratch, *dcap, *doff, *dhalf, *dperm, *dctr, *dlist;
     int rc;
@@ -543,7 +545,7 @@ static int enqueue_wave(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, i
     MSC_HIP(launch_order(n, n_dev, off, shot_idx, n_csr, chan,
                          a.ck_mode == 2 ? c->n_channels : 0, static_cast<int64_t*>(dperm), otmp,
                          ctx->stream));
-    MSC_HIP(fast ? launch_mps_fast_wave(precision, a, grid, ctx->stream)
+    MSC_HIP(fast ? launch_mps_fast(precision, cw, a, grid, ctx->stream)
                  : launch_mps_wave(precision, a, grid, ctx->stream));
     int32_t n_retry = 0;
     MSC_HIP(hipMemcpyAsync(&n_retry, a.retry_count, sizeof(n_retry), hipMemcpyDeviceToHost,
@@ -552,12 +554,13 @@ static int enqueue_wave(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, i
     if (n_retry > 0) {
         RunCfg wg = cfg;
         wg.wave_chi = 0;
+        wg.fast_wide = false;
         rc = enqueue_shots(ctx, c, wg, n_retry, n_csr, off, chan, pauli, shot_idx, out, 0, nullptr,
                            nullptr, 0, nullptr, nullptr, surv, a.retry_list);
         if (rc) return rc;
     }
-    ctx->lx_stats.wave_slots = slots;
-    ctx->lx_stats.wave_retries = n_retry;
+    ctx->lx_stats.wave_slots = cfg.fast_wide ? 0 : slots;
+    ctx->lx_stats.wave_retries = cfg.fast_wide ? 0 : n_retry;
     return MSC_OK;
 }
 
@@ -1000,7 +1003,18 @@ static int sim_cfg(const msc_sim_opts* o, const msc_circuit* c, RunCfg* cfg) {
     else if (o->wave_chi == 0 && o->lds_width == 0 && c && c->calibrated &&
              c->noiseless.chi_peak <= kAutoWaveChi)
         wc = kAutoWaveChi;
+    else if (o->wave_chi == 0 && o->lds_width == 0 && o->large_side == 0 && c && c->calibrated &&
+             fast_path(c) && c->noiseless.chi_peak <= kFastGroupBond) {
+        // wider circuits: the matrix-core kernels of the next caps (49 qubits
+        // on the snake layout, bond 32, 20000 shots: 79.7 ms in the workgroup
+        // kernel, 38.6 here; 256 shots of the 81-qubit patch, bond 64: 1159 ms
+        // and 211), unless the caller sets the workgroup kernel's width or the
+        // engine's
+        wc = c->noiseless.chi_peak <= kFastMidBond ? kFastMidBond : kFastGroupBond;
+        cfg->fast_wide = true;
+    }
     cfg->wave_chi = std::min(wc, cfg->chi_max);
+    if (cfg->wave_chi <= kFastWaveBond) cfg->fast_wide = false;
     default_tiles(cfg->precision, cfg->tiles);
     if (o->autotune_cache) {
         int rc = read_tune_cache(o->autotune_cache, cfg->precision, cfg->tiles);

@@ -139,11 +139,19 @@ int mps_blocks_per_cu(int precision, bool small);
 hipError_t launch_mps_wave(int precision, const MpsArgs& a, int grid, hipStream_t s);
 int mps_wave_blocks_per_cu(int precision);
 constexpr int kWaveTeams = 4;      // shots per workgroup of the wavefront kernel
-// The same on the matrix cores (mps_fast.hip), for slots of bond cap at most
-// kFastWaveBond.
-constexpr int kFastWaveBond = 16;
-hipError_t launch_mps_fast_wave(int precision, const MpsArgs& a, int grid, hipStream_t s);
-int mps_fast_wave_blocks_per_cu(int precision);
+// The same on the matrix cores (mps_fast.hip), by the slots' bond cap: one shot
+// per wavefront up to kFastMidBond (four per workgroup up to kFastWaveBond,
+// kMidTeams above), one per workgroup of kGroupWaves wavefronts up to
+// kFastGroupBond.  The scratch holds 2 side (2 side + 1) doubles per slot, side
+// = 2 cap rounded up to 16, at least 32.
+constexpr int kFastWaveBond = 16, kFastMidBond = 32, kFastGroupBond = 128;
+constexpr int kMidTeams = 7, kGroupWaves = 8;
+struct FastKernel {
+    int teams;           // shots per workgroup
+    int blocks_per_cu;   // resident workgroups per CU
+};
+FastKernel fast_kernel(int cap);
+hipError_t launch_mps_fast(int precision, int cap, const MpsArgs& a, int grid, hipStream_t s);
 
 // Bits of the CSR check flag written by the screen and validation kernels
 enum CsrFlag : int {

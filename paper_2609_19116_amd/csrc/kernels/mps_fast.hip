@@ -33,80 +33,10 @@
 
 #include "kernels.h"
 #include "mps_common.h"
+#include "mps_mfma.h"
 
 namespace msc {
 namespace {
-
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f64x4 mfma(double a, double b, f64x4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
-// The lane's index, opaque to the compiler: what an op derives from it (offsets,
-// lane masks) is computed there and not carried through the whole shot loop
-// in registers.
-__device__ __forceinline__ int op_lane() {
-    int lane = threadIdx.x & 63;
-    asm volatile("" : "+v"(lane));
-    return lane;
-}
-
-// Orders the wavefront's LDS and global accesses for the compiler; the
-// hardware performs one wavefront's accesses to either memory in order.
-__device__ __forceinline__ void wave_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Element i of a tensor plane, by a 32-bit byte offset from its (uniform) base.
-template <typename T>
-__device__ __forceinline__ __attribute__((address_space(1))) T& at(
-    __attribute__((address_space(1))) T* p, uint32_t i) {
-    typedef __attribute__((address_space(1))) char gchar;
-    return *(__attribute__((address_space(1))) T*)((gchar*)p + i * static_cast<uint32_t>(sizeof(T)));
-}
-
-// Four sums over the wavefront, every lane receiving them: a product with
-// ones adds each value over the lane rows, a second one what is left of
-// value j over the columns of its quad's lane j, from where it is spread.
-__device__ __forceinline__ void wave_sum4(double (&v)[4]) {
-    const int j = op_lane() & 3;
-    const f64x4 z = {0.0, 0.0, 0.0, 0.0};
-    double p[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const f64x4 d = mfma(v[i], 1.0, z);
-        p[i] = (d[0] + d[1]) + (d[2] + d[3]);
-    }
-    const double x = (j & 2) ? ((j & 1) ? p[3] : p[2]) : ((j & 1) ? p[1] : p[0]);
-    const double t = mfma(1.0, x, z)[0];
-    v[0] = dpp_move<0x00>(t);
-    v[1] = dpp_move<0x55>(t);
-    v[2] = dpp_move<0xAA>(t);
-    v[3] = dpp_move<0xFF>(t);
-}
-
-// Sum and maximum over the 16 lanes of a row, every lane receiving it.
-__device__ __forceinline__ double row_sum(double v) { return group_sum(v, 16); }
-__device__ __forceinline__ double row_max(double v) {
-    v = fmax(v, dpp_move<0xB1>(v));
-    v = fmax(v, dpp_move<0x4E>(v));
-    v = fmax(v, dpp_move<0x141>(v));
-    return fmax(v, dpp_move<0x140>(v));
-}
-
-// For a condition b on (row g, column q), the number of lanes of this lane's
-// column where it holds.
-__device__ __forceinline__ int column_count(bool b, uint32_t colmask) {
-    const uint64_t m = __ballot(b);
-    return __popc(static_cast<uint32_t>(m) & colmask) +
-           __popc(static_cast<uint32_t>(m >> 32) & colmask);
-}
-
-// A value that is the same in every lane, as a scalar.
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Truncation of the factorisations: keep sigma > tau * sigma_0, at most cap
 // vectors (the slot's bond cap, or chi_max below it).
@@ -116,18 +46,31 @@ struct Trunc {
 };
 
 constexpr int kOps = 16;             // op descriptors held at a time
-constexpr int kVec = 32;             // vectors of a factorisation
-constexpr int kWork = 32 * 33;       // doubles: 32 vectors of 16, or 16 of 32
 constexpr int kStash = 32 * 65;      // doubles: theta put aside in the slot's scratch
 
-// LDS of one wavefront (one base address, constant offsets).
-struct WaveLds {
-    double work[kWork];              // the vectors of a factorisation
-    double nrm[kVec], gre[kVec], gim[kVec];
+// LDS of one shot (one base address, constant offsets): WORK doubles of
+// work area (the vectors of a factorisation), per-vector arrays for VEC
+// vectors, the shot's bonds and outcomes.
+template <int VEC, int WORK>
+struct ShotLds {
+    static constexpr int kVec = VEC, kWork = WORK;
+    double work[WORK];
+    double nrm[VEC], gre[VEC], gim[VEC];
     DevOp ops[kOps];
     int chi[kMaxSites + 4];          // bond dimensions
-    int cnt[kVec], mate[kVec], list[kVec];
+    int cnt[VEC], mate[VEC], list[VEC];
     int laste[kMaxSites];            // last measured outcome per site
+};
+// The same for shots whose wider ops run by a team of NWT wavefronts: the
+// rotations (wc, wr, wi, pair) and ranks of all vectors, and the team's
+// partial results and command.
+template <int VEC, int WORK, int NWT>
+struct TeamLds : ShotLds<VEC, WORK> {
+    double wc[VEC], wr[VEC], wi[VEC];
+    double red[NWT * 4];
+    int pair[VEC], rank[VEC];
+    int flag[NWT];
+    int cmd[4];
 };
 // LDS tables of the workgroup, read-only after the start: 2x2 gates, the
 // monomial 4x4 gates (phase of each row, row that a column feeds) and the
@@ -138,84 +81,16 @@ struct TableLds {
     int g4dst[G4_COUNT * 4];
     int soff[kMaxSites], shalf[kMaxSites];
 };
-typedef __attribute__((address_space(3))) WaveLds LWave;
 typedef __attribute__((address_space(3))) TableLds LTables;
+// one wavefront, slots of bond cap 16: 32 vectors of 16 elements, or 16 of 32
+typedef ShotLds<32, 32 * 33> WaveLds;
 
-
-// Gram tile of the vectors 16 tp + p and 16 tq + q at V (vector v at v * ld, its
-// imaginary part lp further): entry (p, q) is x_p^H y_q, its real and
-// imaginary parts in re and im (len elements, zero-padded to a multiple of 4).
-template <typename DP>
-__device__ __forceinline__ void gram_tile(DP V, int tp, int tq, int ld, int lp, int len, f64x4& re,
-                                          f64x4& im) {
-    const int lane = op_lane(), q = lane & 15, g = lane >> 4;
-    re = f64x4{0.0, 0.0, 0.0, 0.0};
-    im = f64x4{0.0, 0.0, 0.0, 0.0};
-    DP x = V + (16 * tp + q) * ld + g;
-    DP y = V + (16 * tq + q) * ld + g;
-#pragma unroll 2
-    for (int e = 0; e < len; e += 4) {
-        const double xr = x[e], xi = x[lp + e];
-        const double yr = tp == tq ? xr : y[e], yi = tp == tq ? xi : y[lp + e];
-        re = mfma(xr, yr, re);
-        im = mfma(xr, yi, im);
-        re = mfma(xi, yi, re);
-        im = mfma(-xi, yr, im);
-    }
-}
-
-// The diagonal of a diagonal Gram tile: entry (q, q), held by lane row q mod 4
-// in register q / 4, is stored by that lane.
-__device__ __forceinline__ void store_diagonal(const f64x4& re, ldsd* nrm) {
-    const int lane = op_lane(), q = lane & 15, g = lane >> 4;
-    const int r = q >> 2;
-    const double d01 = (r & 1) ? re[1] : re[0], d23 = (r & 1) ? re[3] : re[2];
-    if (g == (q & 3)) nrm[q] = (r & 2) ? d23 : d01;
-}
-
-// One Gram tile's overlapping pairs (rows 16 tp + g + 4 r, columns 16 tq + q,
-// the upper triangle): a pair overlaps when both squared norms exceed floor2
-// and |x^H y|^2 > tol2 |x|^2 |y|^2; cnt[v] counts the vectors v overlaps, mate[v]
-// names one of them and gre/gim[v] hold the pair's x^H y with x its
-// lower-numbered vector.  Returns 0, 1 (found some) or 2 (some vector
-// overlaps more than one).
-__device__ __forceinline__ int tile_overlaps(int tp, int tq, const f64x4& gr, const f64x4& gi,
-                                             LWave* L, double floor2, double tol2) {
-    const int lane = op_lane(), q = lane & 15, g = lane >> 4;
-    const ldsd* nrm = L->nrm;
-    const double b = nrm[16 * tq + q];
-    int any = 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const double a = nrm[16 * tp + g + 4 * r];
-        const double g2 = gr[r] * gr[r] + gi[r] * gi[r];
-        if ((tp < tq || g + 4 * r < q) && a > floor2 && b > floor2 && g2 > tol2 * a * b) {
-            const int p = 16 * tp + g + 4 * r, c = 16 * tq + q;
-            ldsi* cnt = L->cnt;
-            ldsi* mate = L->mate;
-            ldsd* gre = L->gre;
-            ldsd* gim = L->gim;
-            const int o0 = __hip_atomic_fetch_add(cnt + p, 1, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_WAVEFRONT);
-            const int o1 = __hip_atomic_fetch_add(cnt + c, 1, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_WAVEFRONT);
-            any |= (o0 | o1) ? 2 : 1;
-            mate[p] = c;
-            mate[c] = p;
-            gre[p] = gr[r];
-            gre[c] = gr[r];
-            gim[p] = gi[r];
-            gim[c] = gi[r];
-        }
-    }
-    return any;
-}
 
 // The overlapping pairs of the 16 NVT vectors at V and their squared norms
 // (L->nrm).  floor2 < 0 on entry: it becomes rel_floor times the norms' sum,
 // which total receives.  Returns as not_orthogonal.
-template <int NVT, typename DP>
-__device__ __forceinline__ int wave_overlaps(DP V, int ld, int lp, int len, LWave* L,
+template <int NVT, typename DP, typename LW>
+__device__ __forceinline__ int wave_overlaps(DP V, int ld, int lp, int len, LW* L,
                                              double rel_floor, double& floor2, double tol2,
                                              double& total) {
     const int lane = op_lane(), q = lane & 15;
@@ -249,8 +124,8 @@ __device__ __forceinline__ int wave_overlaps(DP V, int ld, int lp, int len, LWav
 
 // Selection of the kept vectors (as select_kept): rank[t] is the position
 // of vector 16 t + q among them, or -1; isq[t], sq[t] its 1/sigma and sigma.
-template <int NVT>
-__device__ __forceinline__ Kept wave_select(LWave* L, double tau2, int capb,
+template <int NVT, typename LW>
+__device__ __forceinline__ Kept wave_select(LW* L, double tau2, int capb,
                                             int (&rank)[NVT], double (&isq)[NVT],
                                             double (&sq)[NVT], int nv) {
     const int lane = op_lane(), q = lane & 15, g = lane >> 4;
@@ -311,8 +186,8 @@ __device__ __forceinline__ Kept wave_select(LWave* L, double tau2, int capb,
 // matching: round-robin sweeps) falls back on the projection of theta, put
 // aside in `stash` (as at V), on the rotated vectors, four MFMAs per 16x16x4
 // block.
-template <typename T, int NVT, typename DP>
-__device__ __forceinline__ bool wave_update(const Trunc P, LWave* L, const LTables* tab,
+template <typename T, int NVT, typename DP, typename LW>
+__device__ __forceinline__ bool wave_update(const Trunc P, LW* L, const LTables* tab,
                                             SiteView<T> A, SiteView<T> B, int k, int dir, int gate_id,
                                             ShotAcc& acc, int cl, int cm, int cr, DP V,
                                             glbd* stash) {
@@ -567,8 +442,8 @@ __device__ __forceinline__ bool wave_update(const Trunc P, LWave* L, const LTabl
 // in the lanes of vector q, which store both at the vector's rank.  Up to 16
 // elements (KS = 4) everything is loaded once and stays in registers; above
 // (KS = 0) the operands are read again for the stores.
-template <typename T, int KS>
-__device__ __forceinline__ bool wave_move(const Trunc P, LWave* L, SiteView<T> A,
+template <typename T, int KS, typename LW>
+__device__ __forceinline__ bool wave_move(const Trunc P, LW* L, SiteView<T> A,
                                           SiteView<T> B, int k, int dir, ShotAcc& acc, int cl,
                                           int cm, int cr) {
     typedef __attribute__((address_space(1))) T gT;
@@ -695,8 +570,8 @@ __device__ __forceinline__ bool wave_move(const Trunc P, LWave* L, SiteView<T> A
 // sum_i conj(psi_i) P[:, i, :] formed in the lanes that hold P in operand
 // layout, the neighbour folded into it by FP64 MFMAs, psi (x) I written to
 // the neighbour's site.  No LDS.
-template <typename T>
-__device__ __forceinline__ void wave_pswap(LWave* L, SiteView<T> Pv, SiteView<T> Ov, int k, int side, int pl,
+template <typename T, typename LW>
+__device__ __forceinline__ void wave_pswap(LW* L, SiteView<T> Pv, SiteView<T> Ov, int k, int side, int pl,
                            int pr, int newb) {
     const int lane = op_lane(), q = lane & 15, g = lane >> 4;
     // side 1: out = O (2 newb x pl) . M (pl x pr), side 0: M (pl x pr) . O (pr x
@@ -797,11 +672,588 @@ __device__ __forceinline__ void wave_pswap(LWave* L, SiteView<T> Pv, SiteView<T>
     wave_order();
 }
 
+// ---------------------------------------------------------------------------
+// The same ops for wider sites, by a team of NWT wavefronts (one shot per
+// team): 16x16 tiles dealt to the wavefronts, FP64 MFMA.  Vectors of a
+// factorisation live at V with a stride of 2 lp + 1 doubles, lp their length
+// rounded up to 16 (LDS when they fit in the work area, else the slot's
+// scratch).  Every wavefront returns the same values.
+
+template <int NWT>
+__device__ __forceinline__ void team_sync() {
+    if constexpr (NWT == 1) wave_order();
+    else __syncthreads();
+}
+template <int NWT>
+__device__ __forceinline__ int team_wave() {
+    if constexpr (NWT == 1) return 0;
+    else return uni(threadIdx.x >> 6);
+}
+
+// OR of a per-lane value's bits 0 and 1 over the team (synchronises).
+template <int NWT, typename LW>
+__device__ __forceinline__ int team_or(LW* L, int v) {
+    const int b = (__ballot(v & 1) ? 1 : 0) | (__ballot(v & 2) ? 2 : 0);
+    if constexpr (NWT == 1) {
+        wave_order();
+        return b;
+    } else {
+        if ((threadIdx.x & 63) == 0) L->flag[threadIdx.x >> 6] = b;
+        __syncthreads();
+        int r = 0;
+        for (int i = 0; i < NWT; ++i) r |= L->flag[i];
+        return uni(r);
+    }
+}
+
+// Sums of four wave-uniform values over the team's wavefronts, in order
+// (synchronises, twice: red may be reused at once).
+template <int NWT, typename LW>
+__device__ __forceinline__ void team_add4(LW* L, double (&v)[4]) {
+    if constexpr (NWT > 1) {
+        const int w = team_wave<NWT>();
+        if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) L->red[4 * w + j] = v[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = 0.0;
+        for (int i = 0; i < NWT; ++i) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] += L->red[4 * i + j];
+        }
+        __syncthreads();
+    }
+}
+
+// Sum of the squared norms nrm[0 .. n), the same order in every wavefront.
+template <typename LW>
+__device__ __forceinline__ double norm_total(LW* L, int n) {
+    double t = 0.0;
+    for (int i = op_lane(); i < n; i += 64) t += L->nrm[i];
+    return wave_sum(t);
+}
+
+// Tile i of the upper triangle above the diagonal of n x n tiles.
+__device__ __forceinline__ void upper_tile(int i, int n, int& tp, int& tq) {
+    tp = 0;
+    while (i >= n - 1 - tp) {
+        i -= n - 1 - tp;
+        ++tp;
+    }
+    tq = tp + 1 + i;
+}
+
+// wave_overlaps over the team, for the nvt Gram tiles a functor computes:
+// gram(tp, tq, re, im).
+template <int NWT, typename LW, typename F>
+__device__ __forceinline__ int team_overlaps(F gram, int nvt, LW* L, double rel_floor,
+                                             double& floor2, double tol2, double& total) {
+    const int w = team_wave<NWT>();
+    f64x4 re, im;
+    for (int t = w; t < nvt; t += NWT) {
+        gram(t, t, re, im);
+        store_diagonal(re, (ldsd*)L->nrm + 16 * t);
+    }
+    for (int i = (int)threadIdx.x % (64 * NWT); i < 16 * nvt; i += 64 * NWT) L->cnt[i] = 0;
+    team_sync<NWT>();
+    if (floor2 < 0.0) {
+        total = norm_total(L, 16 * nvt);
+        floor2 = rel_floor * total;
+    }
+    constexpr int kScope = NWT == 1 ? __HIP_MEMORY_SCOPE_WAVEFRONT : __HIP_MEMORY_SCOPE_WORKGROUP;
+    int any = 0;
+    // the diagonal tiles (a wavefront's last one is still in registers)
+    for (int t = w; t < nvt; t += NWT) {
+        if (nvt > NWT) gram(t, t, re, im);
+        any |= tile_overlaps<kScope>(t, t, re, im, L, floor2, tol2);
+    }
+    const int noff = nvt * (nvt - 1) / 2;
+    for (int i = w; i < noff; i += NWT) {
+        int tp, tq;
+        upper_tile(i, nvt, tp, tq);
+        gram(tp, tq, re, im);
+        any |= tile_overlaps<kScope>(tp, tq, re, im, L, floor2, tol2);
+    }
+    const int r = team_or<NWT>(L, any);
+    return r & 2 ? 2 : r;
+}
+
+// Selection of the kept vectors (as wave_select): rank[v] in LDS.
+template <int NWT, typename LW>
+__device__ __forceinline__ Kept team_select(LW* L, double tau2, int capb, int nv) {
+    const int lane = op_lane(), q = lane & 15, g = lane >> 4;
+    const uint32_t colmask = 0x00010001u << q;
+    const int nvt = (nv + 15) >> 4, w = team_wave<NWT>();
+    double mx = 0.0;
+    for (int i = lane; i < 16 * nvt; i += 64) mx = fmax(mx, sel_norm(L->nrm[i]));
+    mx = wave_max(mx);
+    double v4[4] = {0.0, 0.0, 0.0, 0.0};    // kept, dropped, count kept, above
+    for (int t = w; t < nvt; t += NWT) {
+        const int v = 16 * t + q;
+        const double x = sel_norm(L->nrm[v]);
+        int rk = 0;
+        for (int u = 0; u < nvt; ++u) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double y = sel_norm(L->nrm[16 * u + g + 4 * r]);
+                rk += column_count(y > x || (y == x && 16 * u + g + 4 * r < v), colmask);
+            }
+        }
+        const bool above = v < nv && (x > tau2 * mx || rk == 0);
+        const bool keep = above && rk < capb;
+        if (g == 0) L->rank[v] = keep ? rk : -1;
+        v4[0] += row_sum(keep ? x : 0.0);
+        v4[1] += row_sum(keep ? 0.0 : x);
+        v4[2] += __popc(static_cast<uint32_t>(__ballot(keep)) & 0xFFFFu);
+        v4[3] += __popc(static_cast<uint32_t>(__ballot(above)) & 0xFFFFu);
+    }
+    team_add4<NWT>(L, v4);
+    wave_order();
+    Kept k;
+    k.kept = v4[0];
+    k.dropped = v4[1];
+    k.r = uni(static_cast<int>(v4[2] + 0.5));
+    k.want = uni(static_cast<int>(v4[3] + 0.5));
+    return k;
+}
+
+// What a wide op did, for the shot's record.
+struct WideOp {
+    bool ok;           // false: the slot's bond cap is too small, nothing written
+    bool fast;         // centre move: false if vectors overlap, nothing written
+    int r, sweeps, status;
+    double dropped;
+};
+
+// Two-site update (as wave_update).
+template <typename T, int NWT, typename LW, typename DP>
+__device__ __forceinline__ WideOp team_update(const Trunc P, LW* L, const LTables* tab,
+                                              SiteView<T> A, SiteView<T> B, int dir, int gate_id,
+                                              int cl, int cm, int cr, DP V, glbd* stash) {
+    typedef __attribute__((address_space(1))) T gT;
+    const int lane = op_lane(), q = lane & 15, g = lane >> 4;
+    const int w = team_wave<NWT>();
+    const int m = 2 * cl, n = 2 * cr;
+    const int nv = dir ? n : m, len = dir ? m : n;
+    const int lp = (len + 15) & ~15, ld = 2 * lp + 1;
+    const int nvt = (nv + 15) >> 4;
+    WideOp out{true, true, 0, 0, 0, 0.0};
+
+    // ---- theta = G (A B)
+    const int rt = (m + 15) >> 4, ct = (n + 15) >> 4;
+    for (int tile = w; tile < rt * ct; tile += NWT) {
+        const int tr = tile / ct, R0 = 16 * tr, C0 = 16 * (tile - tr * ct);
+        f64x4 sr = {0.0, 0.0, 0.0, 0.0}, si = {0.0, 0.0, 0.0, 0.0};
+        const int arow = R0 + q, bcol = C0 + q;
+        const bool va = arow < m, vb = bcol < n;
+#pragma unroll 4
+        for (int k0 = 0; k0 < cm; k0 += 4) {
+            const int kk = k0 + g;
+            const bool oa = va && kk < cm, ob = vb && kk < cm;
+            const uint32_t ia = oa ? arow * cm + kk : 0, ib = ob ? kk * n + bcol : 0;
+            const T ar = at(A.re, ia), ai = at(A.im, ia), br = at(B.re, ib), bi = at(B.im, ib);
+            const double xr = oa ? ar : T(0), xi = oa ? ai : T(0);
+            const double yr = ob ? br : T(0), yi = ob ? bi : T(0);
+            sr = mfma(xr, yr, sr);
+            si = mfma(xr, yi, si);
+            sr = mfma(-xi, yi, sr);
+            si = mfma(xi, yr, si);
+        }
+        const int jp = bcol >= cr ? 1 : 0, b = bcol - (jp ? cr : 0);
+        const int o = tab->g4dst[gate_id * 4 + 2 * (g & 1) + jp];
+        const double pr = tab->g4ph[gate_id * 8 + 2 * o], pi = tab->g4ph[gate_id * 8 + 2 * o + 1];
+        const int trow = R0 + (vb ? (g & 2) + (o >> 1) : g);
+        const int tcol = vb ? (o & 1) * cr + b : bcol;
+        DP x = V + (dir ? tcol * ld + trow : trow * ld + tcol);
+        const int step = dir ? 4 : 4 * ld;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            x[0] = pr * sr[r] - pi * si[r];
+            x[lp] = pr * si[r] + pi * sr[r];
+            x += step;
+        }
+    }
+    for (int v = (int)threadIdx.x % (64 * NWT); v < 16 * nvt; v += 64 * NWT) {
+        L->wc[v] = 1.0;
+        L->wr[v] = 0.0;
+        L->wi[v] = 0.0;
+        L->pair[v] = -1;
+    }
+    team_sync<NWT>();
+    const double tau2 = P.tau * P.tau;
+    const double tol = sizeof(T) == sizeof(double) ? static_cast<double>(len) * DBL_EPSILON
+                                                   : 8.0 * static_cast<double>(FLT_EPSILON);
+    const double tol2 = tol * tol;
+    const auto gram = [&](int tp, int tq, f64x4& re, f64x4& im) {
+        gram_tile(V, tp, tq, ld, lp, len, re, im);
+    };
+    double total, floor2 = -1.0;
+    int over = team_overlaps<NWT>(gram, nvt, L, 1e-4 * tau2, floor2, tol2, total);
+    bool closed = true;
+    while (over && out.sweeps < 40) {
+        if (closed && (over == 2 || out.sweeps > 0)) {
+            // theta, put aside for the projection (as in wave_update)
+            closed = false;
+            for (int t = w; t < nvt; t += NWT) {
+                const int v = 16 * t + q, u = L->pair[v];
+                const double c = L->wc[v], br = L->wr[v], bi = L->wi[v];
+                const DP x = V + v * ld + g;
+                const DP y = V + (u < 0 ? v : u) * ld + g;
+                for (int e = 0; e < len; e += 4) {
+                    stash[v * ld + g + e] = c * x[e] - (br * y[e] - bi * y[lp + e]);
+                    stash[v * ld + g + lp + e] = c * x[lp + e] - (br * y[lp + e] + bi * y[e]);
+                }
+            }
+            team_sync<NWT>();
+        }
+        if (over == 1) {
+            // each pair by the lanes of its lower-numbered vector
+            for (int t = w; t < nvt; t += NWT) {
+                const int v = 16 * t + q;
+                const int u = L->cnt[v] ? (int)L->mate[v] : -1;
+                if (u > v) {
+                    const double gr = L->gre[v], gi = L->gim[v];
+                    const double d = L->nrm[u] - L->nrm[v];
+                    const double g2 = gr * gr + gi * gi;
+                    const double q1 = d * d + 4.0 * g2;
+                    const double D = fabs(d) + q1 * rsqrt_nr(q1);
+                    const double rq = rsqrt_nr(D * D + 4.0 * g2);
+                    const double sg = (d >= 0.0 ? 2.0 : -2.0) * rq;
+                    // x' = c x - conj(b) y, y' = c y + b x
+                    const double c = D * rq, br = sg * gr, bi = sg * gi;
+                    if (g == 0) {
+                        L->wc[v] = c;
+                        L->wc[u] = c;
+                        L->wr[v] = -br;
+                        L->wr[u] = br;
+                        L->wi[v] = bi;
+                        L->wi[u] = bi;
+                        L->pair[v] = u;
+                        L->pair[u] = v;
+                    }
+                    DP x = V + v * ld;
+                    DP y = V + u * ld;
+#pragma unroll 2
+                    for (int e = g; e < len; e += 4) {
+                        const double x0 = x[e], x1 = x[lp + e], y0 = y[e], y1 = y[lp + e];
+                        x[e] = c * x0 - (br * y0 + bi * y1);
+                        x[lp + e] = c * x1 - (br * y1 - bi * y0);
+                        y[e] = c * y0 + (br * x0 - bi * x1);
+                        y[lp + e] = c * y1 + (br * x1 + bi * x0);
+                    }
+                }
+            }
+        } else if (w == 0) {
+            int nbad;
+            [[clang::always_inline]] nbad = flagged_list<64>((ldsi*)L->cnt, nv, (ldsi*)L->list, (int*)nullptr);
+            [[clang::always_inline]] jacobi_sweep<64>(V, V + lp, (ldsi*)L->list, nbad, len, ld, floor2, tol);
+        }
+        team_sync<NWT>();
+        ++out.sweeps;
+        double tot;
+        over = team_overlaps<NWT>(gram, nvt, L, 0.0, floor2, tol2, tot);
+    }
+    if (over) out.status |= MSC_SHOT_NOCONV;
+
+    // ---- selection and the new tensors
+    const Kept kp = team_select<NWT>(L, tau2, P.cap, nv);
+    if (kp.want > P.cap && P.cap < P.chi_max) {
+        out.ok = false;
+        return out;
+    }
+    const int r = kp.r;
+    out.r = r;
+    out.dropped = kp.dropped;
+    if (kp.dropped > 1e-12 * total && r == P.cap) out.status |= MSC_SHOT_CHI_CAP;
+    const double renorm = rsqrt_nr(kp.kept);
+    gT* Ure = dir ? A.re : B.re;
+    gT* Uim = dir ? A.im : B.im;
+    gT* Cre = dir ? B.re : A.re;
+    gT* Cim = dir ? B.im : A.im;
+    const int ue = dir ? r : 1, uc = dir ? 1 : n;     // element and vector strides
+    const int cu = dir ? 1 : r, cc = dir ? n : 1;     // index and vector strides
+    for (int t = w; t < nvt; t += NWT) {
+        const int v = 16 * t + q, c = L->rank[v];
+        if (c >= 0) {
+            const double x2 = L->nrm[v], is = rsqrt_nr(x2);
+            const DP x = V + v * ld;
+#pragma unroll 2
+            for (int e = g; e < len; e += 4) {
+                const uint32_t ix = e * ue + c * uc;
+                at(Ure, ix) = T(x[e] * is);
+                at(Uim, ix) = T(x[lp + e] * is);
+            }
+            if (closed) {
+                const double sc = x2 * is * renorm;
+                const T c0 = T(sc * L->wc[v]), c1 = T(sc * L->wr[v]), c2 = T(-(sc * L->wi[v]));
+                const int mt = L->pair[v];
+                for (int u = g; u < nv; u += 4) {
+                    const uint32_t ix = u * cu + c * cc;
+                    at(Cre, ix) = u == v ? c0 : u == mt ? c1 : T(0);
+                    at(Cim, ix) = u == mt ? c2 : T(0);
+                }
+            }
+        }
+    }
+    if (!closed) {
+        for (int i = w; i < nvt * nvt; i += NWT) {
+            // (u, v): theta_u . conj(y_v) over the elements
+            const int tu = i / nvt, t = i - tu * nvt;
+            f64x4 re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+            const glbd* th = stash + (16 * tu + q) * ld + g;
+            const DP y = V + (16 * t + q) * ld + g;
+            for (int e = 0; e < len; e += 4) {
+                const double t0 = th[e], t1 = th[lp + e], y0 = y[e], y1 = y[lp + e];
+                re = mfma(t0, y0, re);
+                im = mfma(t1, y0, im);
+                re = mfma(t1, y1, re);
+                im = mfma(-t0, y1, im);
+            }
+            const int c = L->rank[16 * t + q];
+            const double sc = rsqrt_nr(L->nrm[16 * t + q]) * renorm;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int u = 16 * tu + g + 4 * x;
+                if (c >= 0 && u < nv) {
+                    const uint32_t ix = u * cu + c * cc;
+                    at(Cre, ix) = T(re[x] * sc);
+                    at(Cim, ix) = T(im[x] * sc);
+                }
+            }
+        }
+    }
+    team_sync<NWT>();
+    return out;
+}
+
+// Centre move (as wave_move).  The Gram matrix reads the vectors from the
+// slot; in the usual case (every vector kept, in place) the tensors are scaled
+// where they are, else their new elements go through the slot's scratch.
+template <typename T, int NWT, typename LW>
+__device__ __forceinline__ WideOp team_move(const Trunc P, LW* L, SiteView<T> A, SiteView<T> B,
+                                            int dir, int cl, int cm, int cr, glbd* stash) {
+    typedef __attribute__((address_space(1))) T gT;
+    const int lane = op_lane(), q = lane & 15, g = lane >> 4;
+    const int w = team_wave<NWT>();
+    const int nv = cm, len = dir ? 2 * cl : 2 * cr, wn = dir ? 2 * cr : 2 * cl;
+    const int nvt = (nv + 15) >> 4;
+    gT* Xre = dir ? A.re : B.re;
+    gT* Xim = dir ? A.im : B.im;
+    gT* Nre = dir ? B.re : A.re;
+    gT* Nim = dir ? B.im : A.im;
+    const int xe = dir ? cm : 1, xv = dir ? 1 : len;
+    const int ne = dir ? 1 : cm, nvs = dir ? wn : 1;
+    WideOp out{true, true, 0, 0, 0, 0.0};
+    const auto gram = [&](int tp, int tq, f64x4& re, f64x4& im) {
+        re = f64x4{0.0, 0.0, 0.0, 0.0};
+        im = f64x4{0.0, 0.0, 0.0, 0.0};
+        const int p = 16 * tp + q, c = 16 * tq + q;
+#pragma unroll 4
+        for (int e0 = 0; e0 < len; e0 += 4) {
+            const int e = e0 + g;
+            const bool ip = p < nv && e < len, ic = c < nv && e < len;
+            const uint32_t jp = ip ? p * xv + e * xe : 0, jc = ic ? c * xv + e * xe : 0;
+            const T a0 = at(Xre, jp), a1 = at(Xim, jp), b0 = at(Xre, jc), b1 = at(Xim, jc);
+            const double xr = ip ? a0 : T(0), xi = ip ? a1 : T(0);
+            const double yr = ic ? b0 : T(0), yi = ic ? b1 : T(0);
+            re = mfma(xr, yr, re);
+            im = mfma(xr, yi, im);
+            re = mfma(xi, yi, re);
+            im = mfma(-xi, yr, im);
+        }
+    };
+    const double tau2 = P.tau * P.tau;
+    const double tol = sizeof(T) == sizeof(double) ? static_cast<double>(len) * DBL_EPSILON
+                                                   : 8.0 * static_cast<double>(FLT_EPSILON);
+    double total, floor2 = -1.0;
+    if (team_overlaps<NWT>(gram, nvt, L, 1e-4 * tau2, floor2, tol * tol, total)) {
+        out.fast = false;
+        return out;
+    }
+    const Kept kp = team_select<NWT>(L, tau2, P.cap, nv);
+    const int r = kp.r;
+    out.r = r;
+    out.dropped = kp.dropped;
+    if (kp.dropped > 1e-12 * total && r == P.cap) out.status |= MSC_SHOT_CHI_CAP;
+    const double renorm = rsqrt_nr(kp.kept);
+    int moved = 0;
+    for (int t = w; t < nvt; t += NWT)
+        if (16 * t + q < nv && L->rank[16 * t + q] != 16 * t + q) moved = 1;
+    const bool inplace = team_or<NWT>(L, moved) == 0;
+    const int ue = dir ? r : 1, uv = dir ? 1 : len;
+    const int me = dir ? 1 : r, mv = dir ? wn : 1;
+    glbd* sx = stash;
+    glbd* sn = stash + 2 * (size_t)r * len;
+    for (int t = w; t < nvt; t += NWT) {
+        const int v = 16 * t + q, c = v < nv ? (int)L->rank[v] : -1;
+        if (c >= 0) {
+            const double x2 = L->nrm[v], is = rsqrt_nr(x2), sc = x2 * is * renorm;
+#pragma unroll 2
+            for (int e = g; e < len; e += 4) {
+                const uint32_t ix = v * xv + e * xe;
+                const double a = at(Xre, ix), b = at(Xim, ix);
+                if (inplace) {
+                    at(Xre, ix) = T(a * is);
+                    at(Xim, ix) = T(b * is);
+                } else {
+                    sx[e * ue + c * uv] = a * is;
+                    sx[(size_t)r * len + e * ue + c * uv] = b * is;
+                }
+            }
+#pragma unroll 2
+            for (int e = g; e < wn; e += 4) {
+                const uint32_t ix = v * nvs + e * ne;
+                const double a = at(Nre, ix), b = at(Nim, ix);
+                if (inplace) {
+                    at(Nre, ix) = T(a * sc);
+                    at(Nim, ix) = T(b * sc);
+                } else {
+                    sn[e * me + c * mv] = a * sc;
+                    sn[(size_t)r * wn + e * me + c * mv] = b * sc;
+                }
+            }
+        }
+    }
+    team_sync<NWT>();
+    if (!inplace) {
+        const int tid = (int)threadIdx.x % (64 * NWT);
+        for (int i = tid; i < r * len; i += 64 * NWT) {
+            at(Xre, i) = T(sx[i]);
+            at(Xim, i) = T(sx[(size_t)r * len + i]);
+        }
+        for (int i = tid; i < r * wn; i += 64 * NWT) {
+            at(Nre, i) = T(sn[i]);
+            at(Nim, i) = T(sn[(size_t)r * wn + i]);
+        }
+        team_sync<NWT>();
+    }
+    return out;
+}
+
+// Product swap (as wave_pswap), with M at Mp (2 pl pr doubles: the work area
+// or the slot's scratch).
+template <typename T, int NWT, typename LW, typename DP>
+__device__ __forceinline__ void team_pswap(LW* L, SiteView<T> Pv, SiteView<T> Ov, int side, int pl,
+                                           int pr, int newb, DP Mp) {
+    const int lane = op_lane(), q = lane & 15, g = lane >> 4;
+    const int w = team_wave<NWT>();
+    const int nk = side ? pl : pr, nm = side ? pr : pl, no = 2 * newb;
+    const int mk = side ? 2 * pr : 1, mq = side ? 1 : 2 * pr;     // strides in P
+    const int ok = side ? 1 : no, oq = side ? pl : 1;             // strides in O
+    const int kt = (nk + 3) >> 2, mt = (nm + 15) >> 4;
+    double r4[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i = w; i < kt * mt; i += NWT) {
+        const int a = i / mt, kk = 4 * a + g, c = 16 * (i - a * mt) + q;
+        if (kk < nk && c < nm) {
+            const uint32_t i0 = kk * mk + c * mq;
+            const double x0r = at(Pv.re, i0), x0i = at(Pv.im, i0);
+            const double x1r = at(Pv.re, i0 + pr), x1i = at(Pv.im, i0 + pr);
+            r4[0] += x0r * x0r + x0i * x0i;
+            r4[1] += x1r * x1r + x1i * x1i;
+            r4[2] += x0r * x1r + x0i * x1i;     // rho01 = x0 conj(x1)
+            r4[3] += x0i * x1r - x0r * x1i;
+        }
+    }
+    wave_sum4(r4);
+    team_add4<NWT>(L, r4);
+    const bool one = r4[1] > r4[0];
+    const double pn = one ? r4[1] : r4[0];
+    const double pd = rsqrt_nr(pn * (r4[0] + r4[1]));
+    const double s0r = (one ? r4[2] : pn) * pd, s0i = one ? r4[3] * pd : 0.0;
+    const double s1r = (one ? pn : r4[2]) * pd, s1i = one ? 0.0 : -(r4[3] * pd);
+    for (int i = w; i < kt * mt; i += NWT) {
+        const int a = i / mt, kk = 4 * a + g, c = 16 * (i - a * mt) + q;
+        if (kk < nk && c < nm) {
+            const uint32_t i0 = kk * mk + c * mq;
+            const double x0r = at(Pv.re, i0), x0i = at(Pv.im, i0);
+            const double x1r = at(Pv.re, i0 + pr), x1i = at(Pv.im, i0 + pr);
+            Mp[kk * nm + c] = s0r * x0r + s0i * x0i + s1r * x1r + s1i * x1i;
+            Mp[nk * nm + kk * nm + c] = s0r * x0i - s0i * x0r + s1r * x1i - s1i * x1r;
+        }
+    }
+    team_sync<NWT>();
+    const int rows = side ? no : pl, cols = side ? pr : no;
+    const int ct = (cols + 15) >> 4, nt = ((rows + 15) >> 4) * ct;
+    for (int i = w; i < nt; i += NWT) {
+        const int tr = i / ct, R0 = 16 * tr, C0 = 16 * (i - tr * ct);
+        // O's outer index and M's other index of this lane
+        const int o = (side ? R0 : C0) + q, c = (side ? C0 : R0) + q;
+        f64x4 re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int k0 = 0; k0 < nk; k0 += 4) {
+            const int kk = k0 + g;
+            const bool io = o < no && kk < nk, ic = c < nm && kk < nk;
+            const uint32_t jo = io ? kk * ok + o * oq : 0;
+            const int jc = ic ? kk * nm + c : 0;
+            const T o0 = at(Ov.re, jo), o1 = at(Ov.im, jo);
+            const double m0 = Mp[jc], m1 = Mp[nk * nm + jc];
+            const double xr = io ? o0 : T(0), xi = io ? o1 : T(0);
+            const double yr = ic ? m0 : 0.0, yi = ic ? m1 : 0.0;
+            const double ar = side ? xr : yr, ai = side ? xi : yi;
+            const double br = side ? yr : xr, bi = side ? yi : xi;
+            re = mfma(ar, br, re);
+            im = mfma(ar, bi, im);
+            re = mfma(-ai, bi, re);
+            im = mfma(ai, br, im);
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int row = R0 + g + 4 * x, col = C0 + q;
+            if (row < rows && col < cols) {
+                const uint32_t ix = row * cols + col;
+                at(Pv.re, ix) = T(re[x]);
+                at(Pv.im, ix) = T(im[x]);
+            }
+        }
+    }
+    team_sync<NWT>();
+    // the unentangled qubit on the other site: psi (x) identity
+    for (int row = 4 * w + g; row < no; row += 4 * NWT) {          // (a, i)
+        for (int c = q; c < newb; c += 16) {
+            const bool diag = c == (row >> 1), i = row & 1;
+            const uint32_t ix = row * newb + c;
+            at(Ov.re, ix) = T(diag ? (i ? s1r : s0r) : 0.0);
+            at(Ov.im, ix) = T(diag ? (i ? s1i : s0i) : 0.0);
+        }
+    }
+    team_sync<NWT>();
+}
+
+// A wide op (kind OP_MOVE, OP_SWAPP or OP_G2 of sites a, a + 1; b its
+// direction or side) by the whole team.  A product swap's new bond is set
+// here; the caller sets the others' from the result.
+template <typename T, int NWT, typename LW>
+__device__ __forceinline__ WideOp wide_op(const Trunc P, LW* L, const LTables* tab, int kind, int a,
+                                          int b, int gate_id, SiteView<T> A, SiteView<T> B,
+                                          glbd* scr) {
+    const int cl = uni(L->chi[a]), cm = uni(L->chi[a + 1]), cr = uni(L->chi[a + 2]);
+    if (kind == OP_SWAPP) {
+        const int pl = b ? cm : cl, pr = b ? cr : cm, newb = b ? cl : cr;
+        const SiteView<T> Pv = b ? B : A, Ov = b ? A : B;
+        if (2 * pl * pr <= LW::kWork)
+            team_pswap<T, NWT>(L, Pv, Ov, b, pl, pr, newb, (ldsd*)L->work);
+        else
+            team_pswap<T, NWT>(L, Pv, Ov, b, pl, pr, newb, scr);
+        return WideOp{true, true, newb, 0, 0, 0.0};
+    }
+    if (kind == OP_MOVE) return team_move<T, NWT>(P, L, A, B, b, cl, cm, cr, scr);
+    const int nv = 2 * (b ? cr : cl), len = 2 * (b ? cl : cr);
+    const int rows = (nv + 15) & ~15, ld = 2 * ((len + 15) & ~15) + 1;
+    if (rows * ld <= LW::kWork)
+        return team_update<T, NWT>(P, L, tab, A, B, b, gate_id, cl, cm, cr, (ldsd*)L->work, scr);
+    return team_update<T, NWT>(P, L, tab, A, B, b, gate_id, cl, cm, cr, scr + (size_t)rows * ld, scr);
+}
+
 // The shots of one wavefront in its slot: each from its fork point (or from
 // |0...0>) through the op stream to its result, op by op.  EXTRA compiles in
-// checkpoint recording and segment reach.
-template <typename T, bool EXTRA>
-__device__ __forceinline__ void run_wave(const MpsArgs& P, LWave* L, const LTables* tab, int team) {
+// checkpoint recording and segment reach.  NWT > 0: ops on bonds above 16 run
+// by the team of NWT wavefronts this one leads (a wide centre move counts as
+// the identity update it stands for, as in the workgroup kernel, whose LDS
+// vectors hold 32); NWT = 0: the slots' bonds stay within 16.
+template <typename T, bool EXTRA, int NWT, typename LW>
+__device__ __forceinline__ void run_wave(const MpsArgs& P, LW* L, const LTables* tab, int team) {
     typedef __attribute__((address_space(1))) T gT;
     const int lane = threadIdx.x & 63;
     const int N = P.n_sites;
@@ -816,6 +1268,23 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LWave* L, const LTabl
         return v;
     };
     const auto chi = [&](int k) { return uni(L->chi[k]); };
+    const int lane0 = lane == 0;
+    // hands a wide op to the team
+    const auto wide = [&](int kind, int a, int b, int gate_id) {
+        if constexpr (NWT > 1) {
+            if (lane0) {
+                L->cmd[0] = kind;
+                L->cmd[1] = a;
+                L->cmd[2] = b;
+                L->cmd[3] = gate_id;
+            }
+            __syncthreads();
+        }
+        if constexpr (NWT > 0)
+            return wide_op<T, NWT>(trunc, L, tab, kind, a, b, gate_id, site(a), site(a + 1), scr);
+        else
+            return WideOp{};
+    };
     const int64_t n_run = P.n_dev ? min(*P.n_dev, P.n_shots) : P.n_shots;
     for (int64_t j = wave_fetch(P.next); j < n_run; j = wave_fetch(P.next)) {
         const int64_t it = P.perm ? P.perm[j] : j;
@@ -864,6 +1333,7 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LWave* L, const LTabl
                 for (int k = 0; k < N; ++k) {
                     const int ne = chi(k) * 2 * chi(k + 1);
                     SiteView<T> v = site(k);
+#pragma unroll 4
                     for (int i = lane; i < ne; i += 64) {
                         v.re[i] = src[i];
                         v.im[i] = src[ne + i];
@@ -948,18 +1418,43 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LWave* L, const LTabl
             int gate_id = aux;
             if (kind == OP_MOVE) {
                 const int cl = chi(a), cm = chi(a + 1), cr = chi(a + 2);
-                const SiteView<T> A = site(a), B = site(a + 1);
-                const bool fast = max(cl, cr) <= 8
-                                      ? wave_move<T, 4>(trunc, L, A, B, a, b, acc, cl, cm, cr)
-                                      : wave_move<T, 0>(trunc, L, A, B, a, b, acc, cl, cm, cr);
+                bool fast;
+                if (NWT > 0 && (cm > 16 || max(cl, cr) > 16)) {
+                    const WideOp o = wide(OP_MOVE, a, b, 0);
+                    fast = o.fast;
+                    if (fast) {
+                        acc.disc += o.dropped;
+                        acc.status |= o.status;
+                        if (lane0) L->chi[a + 1] = o.r;
+                        if (cm > 32 || (b ? cl : cr) > 16) {
+                            // an identity update in the records
+                            const double dl = cl, dm = cm, dr = cr, dk = o.r;
+                            ++acc.n2q;
+                            acc.chi_peak = max(acc.chi_peak, o.r);
+                            acc.flops += 32.0 * dl * dm * dr + 32.0 * dl * dl * dr +
+                                         32.0 * dk * dl * dr + 104.0 * dl * dl * dl;
+                        }
+                        wave_order();
+                    }
+                } else {
+                    const SiteView<T> A = site(a), B = site(a + 1);
+                    fast = max(cl, cr) <= 8 ? wave_move<T, 4>(trunc, L, A, B, a, b, acc, cl, cm, cr)
+                                            : wave_move<T, 0>(trunc, L, A, B, a, b, acc, cl, cm, cr);
+                }
                 if (!fast) {
                     twosite = true;
                     gate_id = G4_I;
                 }
             } else if (kind == OP_SWAPP) {
                 const int ps = a + b, os = a + 1 - b;
-                wave_pswap<T>(L, site(ps), site(os), a, b, chi(ps), chi(ps + 1),
-                              b ? chi(a) : chi(a + 2));
+                const int pl = chi(ps), pr = chi(ps + 1), newb = b ? chi(a) : chi(a + 2);
+                if (NWT > 0 && max(max(pl, pr), newb) > 16) {
+                    wide(OP_SWAPP, a, b, 0);
+                    if (lane0) L->chi[a + 1] = newb;
+                    wave_order();
+                } else {
+                    wave_pswap<T>(L, site(ps), site(os), a, b, pl, pr, newb);
+                }
             } else if (kind == OP_G1 || kind == OP_FAULT || kind == OP_FAULT3 || kind == OP_RESET) {
                 // ---- local 2x2 on one site (two for a two-qubit fault)
                 int g0 = -1, g1 = -1;
@@ -993,9 +1488,10 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LWave* L, const LTabl
                     const SiteView<T> v = site(k);
                     const int cl = chi(k), cr = chi(k + 1);
                     const int l = op_lane(), q = l & 15, g = l >> 4;
-                    if (q < cr) {
+                    for (int y = q; y < cr; y += 16) {
+#pragma unroll 4
                         for (int x = g; x < cl; x += 4) {
-                            const uint32_t i0 = x * 2 * cr + q, i1 = i0 + cr;
+                            const uint32_t i0 = x * 2 * cr + y, i1 = i0 + cr;
                             const double x0r = at(v.re, i0), x0i = at(v.im, i0), x1r = at(v.re, i1),
                                          x1i = at(v.im, i1);
                             at(v.re, i0) = T(m0 * x0r - m1 * x0i + m2 * x1r - m3 * x1i);
@@ -1013,18 +1509,32 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LWave* L, const LTabl
                 const int l = op_lane(), q = l & 15, g = l >> 4;
                 double pe2 = 0.0, po2 = 0.0;          // squared norms of the two outcomes
                 T xr[4], xi[4];
+                const bool wide_site = NWT > 0 && max(cl, cr) > 16;
+                if (!wide_site) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int x = 4 * t + g;
-                    xr[t] = T(0);
-                    xi[t] = T(0);
-                    if (q < cr && x < cl) {
-                        const uint32_t ie = (x * 2 + e) * cr + q, io = (x * 2 + 1 - e) * cr + q;
-                        xr[t] = at(v.re, ie);
-                        xi[t] = at(v.im, ie);
-                        const double er = xr[t], ei = xi[t], fr = at(v.re, io), fi = at(v.im, io);
-                        pe2 += er * er + ei * ei;
-                        po2 += fr * fr + fi * fi;
+                    for (int t = 0; t < 4; ++t) {
+                        const int x = 4 * t + g;
+                        xr[t] = T(0);
+                        xi[t] = T(0);
+                        if (q < cr && x < cl) {
+                            const uint32_t ie = (x * 2 + e) * cr + q, io = (x * 2 + 1 - e) * cr + q;
+                            xr[t] = at(v.re, ie);
+                            xi[t] = at(v.im, ie);
+                            const double er = xr[t], ei = xi[t], fr = at(v.re, io), fi = at(v.im, io);
+                            pe2 += er * er + ei * ei;
+                            po2 += fr * fr + fi * fi;
+                        }
+                    }
+                } else {
+                    for (int y = q; y < cr; y += 16) {
+#pragma unroll 2
+                        for (int x = g; x < cl; x += 4) {
+                            const uint32_t ie = (x * 2 + e) * cr + y, io = (x * 2 + 1 - e) * cr + y;
+                            const double er = at(v.re, ie), ei = at(v.im, ie);
+                            const double fr = at(v.re, io), fi = at(v.im, io);
+                            pe2 += er * er + ei * ei;
+                            po2 += fr * fr + fi * fi;
+                        }
                     }
                 }
                 pe2 = wave_sum(pe2);
@@ -1049,15 +1559,28 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LWave* L, const LTabl
                 p_acc *= pe;
                 meas_done = aux + 1;
                 const double sc = rsqrt_nr(pe2);
+                if (!wide_site) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int x = 4 * t + g;
-                    if (q < cr && x < cl) {
-                        const uint32_t ie = (x * 2 + e) * cr + q, io = (x * 2 + 1 - e) * cr + q;
-                        at(v.re, ie) = T(static_cast<double>(xr[t]) * sc);
-                        at(v.im, ie) = T(static_cast<double>(xi[t]) * sc);
-                        at(v.re, io) = T(0);
-                        at(v.im, io) = T(0);
+                    for (int t = 0; t < 4; ++t) {
+                        const int x = 4 * t + g;
+                        if (q < cr && x < cl) {
+                            const uint32_t ie = (x * 2 + e) * cr + q, io = (x * 2 + 1 - e) * cr + q;
+                            at(v.re, ie) = T(static_cast<double>(xr[t]) * sc);
+                            at(v.im, ie) = T(static_cast<double>(xi[t]) * sc);
+                            at(v.re, io) = T(0);
+                            at(v.im, io) = T(0);
+                        }
+                    }
+                } else {
+                    for (int y = q; y < cr; y += 16) {
+#pragma unroll 2
+                        for (int x = g; x < cl; x += 4) {
+                            const uint32_t ie = (x * 2 + e) * cr + y, io = (x * 2 + 1 - e) * cr + y;
+                            at(v.re, ie) = T(static_cast<double>(at(v.re, ie)) * sc);
+                            at(v.im, ie) = T(static_cast<double>(at(v.im, ie)) * sc);
+                            at(v.re, io) = T(0);
+                            at(v.im, io) = T(0);
+                        }
                     }
                 }
                 if (lane == 0) L->laste[a] = e;
@@ -1075,9 +1598,9 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LWave* L, const LTabl
                 }
                 double r[4] = {0.0, 0.0, 0.0, 0.0};   // r00, r11, Re r01, Im r01
                 const int l = op_lane(), q = l & 15, g = l >> 4;
-                if (q < cr) {
+                for (int y = q; y < cr; y += 16) {
                     for (int x = g; x < cl; x += 4) {
-                        const uint32_t i0 = x * 2 * cr + q, i1 = i0 + cr;
+                        const uint32_t i0 = x * 2 * cr + y, i1 = i0 + cr;
                         const double x0r = at(v.re, i0), x0i = at(v.im, i0), x1r = at(v.re, i1), x1i = at(v.im, i1);
                         r[0] += x0r * x0r + x0i * x0i;
                         r[1] += x1r * x1r + x1i * x1i;
@@ -1101,15 +1624,31 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LWave* L, const LTabl
                 const int nv = 2 * (b ? cr : cl), len = 2 * (b ? cl : cr);
                 const SiteView<T> A = site(a), B = site(a + 1);
                 bool ok;
-                if (nv <= 16)
+                if (nv <= 16 && len <= 32)
                     ok = wave_update<T, 1>(trunc, L, tab, A, B, a, b, gate_id, acc, cl, cm, cr,
                                            (ldsd*)L->work, scr);
-                else if (len <= 16)
+                else if (nv <= 32 && len <= 16)
                     ok = wave_update<T, 2>(trunc, L, tab, A, B, a, b, gate_id, acc, cl, cm, cr,
                                            (ldsd*)L->work, scr);
-                else
+                else if constexpr (NWT == 0)
                     ok = wave_update<T, 2>(trunc, L, tab, A, B, a, b, gate_id, acc, cl, cm, cr,
                                            scr + kStash, scr);
+                else {
+                    const WideOp o = wide(OP_G2, a, b, gate_id);
+                    ok = o.ok;
+                    if (ok) {
+                        const double dl = cl, dm = cm, dr = cr, dk = o.r;
+                        acc.disc += o.dropped;
+                        acc.status |= o.status;
+                        acc.sweeps += o.sweeps;
+                        acc.chi_peak = max(acc.chi_peak, o.r);
+                        ++acc.n2q;
+                        acc.flops += 32.0 * dl * dm * dr + 32.0 * dl * dl * dr + 32.0 * dk * dl * dr +
+                                     104.0 * dl * dl * dl;
+                        if (lane0) L->chi[a + 1] = o.r;
+                        wave_order();
+                    }
+                }
                 if (!ok) {
                     // a larger slot is needed: the shot is queued for the
                     // workgroup kernel, which runs it again from its start
@@ -1137,18 +1676,42 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LWave* L, const LTabl
         }
         wave_order();
     }
+    if constexpr (NWT > 1) {
+        if (lane0) L->cmd[0] = -1;
+        __syncthreads();
+    }
 }
 
-template <typename T, bool EXTRA>
-__global__ __launch_bounds__(NT, 3) void mps_fast_wave_kernel(MpsArgs P) {
-    __shared__ __align__(16) WaveLds s_wave[NW];
-    __shared__ __align__(16) TableLds s_tab;
+// The other wavefronts of a team: they join every wide op until the leader
+// has no shots left.
+template <typename T, int NWT, typename LW>
+__device__ __forceinline__ void follow(const MpsArgs& P, LW* L, const LTables* tab, int team) {
+    typedef __attribute__((address_space(1))) T gT;
+    gT* slot = to_glb(static_cast<T*>(P.arena) + (size_t)team * P.slot_stride);
+    glbd* scr = to_glb(P.scratch + (size_t)team * P.scratch_stride);
+    const Trunc trunc{P.tau, P.chi_max, P.n_sites > 1 ? min(P.chi_max, P.cap[1]) : 1};
+    for (;;) {
+        __syncthreads();
+        const int kind = uni(L->cmd[0]), a = uni(L->cmd[1]), b = uni(L->cmd[2]),
+                  gate_id = uni(L->cmd[3]);
+        if (kind < 0) return;
+        SiteView<T> A, B;
+        A.re = slot + uni(tab->soff[a]);
+        A.im = A.re + uni(tab->shalf[a]);
+        B.re = slot + uni(tab->soff[a + 1]);
+        B.im = B.re + uni(tab->shalf[a + 1]);
+        wide_op<T, NWT>(trunc, L, tab, kind, a, b, gate_id, A, B, scr);
+    }
+}
+
+// The workgroup's tables (nt threads; ends synchronised).
+__device__ __forceinline__ void fill_tables(const MpsArgs& P, TableLds& s_tab, int nt) {
     const int tid = threadIdx.x;
-    for (int k = tid; k < P.n_sites; k += NT) {
+    for (int k = tid; k < P.n_sites; k += nt) {
         s_tab.soff[k] = static_cast<int>(P.site_off[k]);
         s_tab.shalf[k] = static_cast<int>(P.site_half[k]);
     }
-    for (int i = tid; i < G1_COUNT * 8; i += NT) s_tab.g1[i] = P.g1[i];
+    for (int i = tid; i < G1_COUNT * 8; i += nt) s_tab.g1[i] = P.g1[i];
     if (tid < G4_COUNT * 4) {
         // the nonzero of each row of each monomial 4x4 gate
         const double* m = P.g4 + (tid >> 2) * 32 + (tid & 3) * 8;
@@ -1160,39 +1723,80 @@ __global__ __launch_bounds__(NT, 3) void mps_fast_wave_kernel(MpsArgs P) {
         s_tab.g4ph[2 * tid + 1] = m[2 * src + 1];
     }
     __syncthreads();
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    run_wave<T, EXTRA>(P, (LWave*)(s_wave + w), (LTables*)&s_tab, blockIdx.x * NW + w);
+}
+
+template <typename T, bool EXTRA>
+__global__ __launch_bounds__(NT, 3) void mps_fast_wave_kernel(MpsArgs P) {
+    __shared__ __align__(16) WaveLds s_wave[NW];
+    __shared__ __align__(16) TableLds s_tab;
+    fill_tables(P, s_tab, NT);
+    const int w = uni(threadIdx.x >> 6);
+    run_wave<T, EXTRA, 0>(P, (__attribute__((address_space(3))) WaveLds*)(s_wave + w),
+                          (LTables*)&s_tab, blockIdx.x * NW + w);
+}
+
+// Bond cap 32: still one shot per wavefront, seven per workgroup and CU (LDS:
+// 64 vectors of 16 elements, 32 of 32 or 16 of 64 each; wider factorisations
+// in the slot's scratch).
+typedef TeamLds<64, 64 * 33, 1> MidLds;
+template <typename T>
+__global__ __launch_bounds__(64 * kMidTeams, 1) void mps_fast_mid_kernel(MpsArgs P) {
+    __shared__ __align__(16) MidLds s_wave[kMidTeams];
+    __shared__ __align__(16) TableLds s_tab;
+    fill_tables(P, s_tab, 64 * kMidTeams);
+    const int w = uni(threadIdx.x >> 6);
+    run_wave<T, true, 1>(P, (__attribute__((address_space(3))) MidLds*)(s_wave + w),
+                         (LTables*)&s_tab, blockIdx.x * kMidTeams + w);
+}
+
+// Bond cap 128: one shot per workgroup of kGroupWaves wavefronts, one
+// workgroup per CU (LDS: 128 vectors of 64 elements or 64 of 128).
+typedef TeamLds<256, 128 * 129, kGroupWaves> GroupLds;
+template <typename T>
+__global__ __launch_bounds__(64 * kGroupWaves, 1) void mps_fast_group_kernel(MpsArgs P) {
+    __shared__ __align__(16) GroupLds s_shot;
+    __shared__ __align__(16) TableLds s_tab;
+    fill_tables(P, s_tab, 64 * kGroupWaves);
+    auto* L = (__attribute__((address_space(3))) GroupLds*)&s_shot;
+    if (uni(threadIdx.x >> 6) == 0)
+        run_wave<T, true, kGroupWaves>(P, L, (LTables*)&s_tab, blockIdx.x);
+    else
+        follow<T, kGroupWaves>(P, L, (LTables*)&s_tab, blockIdx.x);
 }
 
 }  // namespace
 
-int mps_fast_wave_blocks_per_cu(int precision) {
-    int b = 0;
-    hipError_t e = precision == MSC_FP64
-                       ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                             &b, mps_fast_wave_kernel<double, true>, NT, 0)
-                       : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                             &b, mps_fast_wave_kernel<float, true>, NT, 0);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return 1;
-    }
-    return b < 1 ? 1 : b;
+FastKernel fast_kernel(int cap) {
+    FastKernel k{};
+    k.teams = cap <= kFastWaveBond ? kWaveTeams : cap <= kFastMidBond ? kMidTeams : 1;
+    k.blocks_per_cu = cap <= kFastWaveBond ? 3 : 1;
+    return k;
 }
 
-hipError_t launch_mps_fast_wave(int precision, const MpsArgs& a, int grid, hipStream_t s) {
+hipError_t launch_mps_fast(int precision, int cap, const MpsArgs& a, int grid, hipStream_t s) {
     static_assert(kWaveTeams == NW, "one team per wavefront");
-    if (!a.next || !a.retry_count || !a.retry_list || a.calibrate || a.state ||
-        a.scratch_stride < kStash + 32 * 65)
+    static_assert(sizeof(WaveLds) * NW + sizeof(TableLds) <= 160 * 1024 / 3, "three workgroups per CU");
+    static_assert(sizeof(MidLds) * kMidTeams + sizeof(TableLds) <= 160 * 1024, "LDS of one CU");
+    static_assert(sizeof(GroupLds) + sizeof(TableLds) <= 160 * 1024, "LDS of one CU");
+    // vectors and theta's copy of the widest factorisation, in the scratch
+    const int64_t side = cap <= kFastWaveBond ? 32 : 2 * ((cap + 7) & ~7);
+    if (!a.next || !a.retry_count || !a.retry_list || a.calibrate || a.state || cap < 1 ||
+        cap > kFastGroupBond || a.scratch_stride < 2 * side * (2 * side + 1))
         return hipErrorInvalidValue;
-    const bool extra = a.surv != nullptr || a.ck_mode == 1;
-    const auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(NT), 0, s, a);
+    const auto go = [&](auto kernel, int nt) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(nt), 0, s, a);
         return hipGetLastError();
     };
-    if (precision == MSC_FP64)
-        return extra ? go(mps_fast_wave_kernel<double, true>) : go(mps_fast_wave_kernel<double, false>);
-    return extra ? go(mps_fast_wave_kernel<float, true>) : go(mps_fast_wave_kernel<float, false>);
+    const bool d = precision == MSC_FP64;
+    if (cap > kFastMidBond)
+        return d ? go(mps_fast_group_kernel<double>, 64 * kGroupWaves)
+                 : go(mps_fast_group_kernel<float>, 64 * kGroupWaves);
+    if (cap > kFastWaveBond)
+        return d ? go(mps_fast_mid_kernel<double>, 64 * kMidTeams)
+                 : go(mps_fast_mid_kernel<float>, 64 * kMidTeams);
+    const bool extra = a.surv != nullptr || a.ck_mode == 1;
+    if (d) return extra ? go(mps_fast_wave_kernel<double, true>, NT) : go(mps_fast_wave_kernel<double, false>, NT);
+    return extra ? go(mps_fast_wave_kernel<float, true>, NT) : go(mps_fast_wave_kernel<float, false>, NT);
 }
 
 }  // namespace msc
