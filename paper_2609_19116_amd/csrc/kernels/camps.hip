@@ -31,6 +31,7 @@
 #include <cstdint>
 
 #include "kernels.h"
+#include "mps_mfma.h"
 
 namespace msc {
 namespace {
@@ -121,14 +122,22 @@ __device__ __forceinline__ void pauli_elem(int x, int z, int i, int& src, double
 
 // Work matrices of one SVD: W (len x nv, column-major, leading dimension
 // ldw) and V (nv x nv, column-major, ldv), in LDS when they fit (len <=
-// kWaveLen, nv <= kWaveCols: one wavefront factorises them without
-// workgroup barriers) and otherwise in the slot's global scratch.
+// kWaveLen, nv <= kWaveCols; odd leading dimensions, so that the columns lie
+// on different banks) and otherwise in the slot's global scratch.
 constexpr int kWaveLen = 64, kWaveCols = 32;
+constexpr int kLdsW = kWaveLen + 1, kLdsV = kWaveCols + 1;
 struct WV {
     double *wr, *wi, *vr, *vi;
     int ldw, ldv;
     bool wave;
 };
+// The overlapping pairs of an LDS factorisation's columns (tile_overlaps)
+struct PairLds {
+    double nrm[kWaveCols], gre[kWaveCols], gim[kWaveCols];
+    int cnt[kWaveCols], mate[kWaveCols];
+    int over;
+};
+typedef __attribute__((address_space(3))) PairLds LPair;
 
 // a fence that makes this wavefront's LDS and global writes visible to all
 // of its lanes, without a workgroup barrier
@@ -191,49 +200,107 @@ __device__ __forceinline__ void rr_pair(int i, int t, int m, int& p, int& q) {
 }
 
 // One-sided Jacobi on the columns of W: W <- W V with V unitary and the
-// columns of the result mutually orthogonal.  Whole workgroup; the LDS
-// variant runs on wavefront 0 alone.  Returns the sweeps used (-1: no
-// convergence).
-__device__ int jacobi_cols(const WV& w, int len, int nv, int* s_flag) {
+// columns of the result mutually orthogonal.  Whole workgroup.  Returns the
+// sweeps used (-1: no convergence).
+//
+// In LDS, each sweep starts from the Gram matrix of the columns on FP64 MFMA:
+// pairs with |x^H y| <= (len + 16) eps |x| |y| count as orthogonal, and
+// columns below a tenth of the threshold thr * sigma_max that the caller drops
+// by as zero.  When every overlapping column has exactly one mate, which is
+// the usual case, all pairs rotate in one step; else one round-robin sweep
+// by wavefront 0.  A round-robin sweep over 32 columns is 31 dependent steps
+// and needed a second one to find nothing left: 256 49-qubit shots took 185
+// ms, now @@ (one shot's latency).  The columns' squared norms are left in
+// J.nrm.
+__device__ int jacobi_cols(const WV& w, int len, int nv, double thr, int* s_flag, LPair* J) {
     const int tid = threadIdx.x;
     if (w.wave) {
-        __shared__ int s_sw;
-        if (tid < 64) {
-            for (int e = tid; e < nv * nv; e += 64) {
-                const int col = e / nv, row = e - col * nv;
-                w.vr[col * w.ldv + row] = row == col ? 1.0 : 0.0;
-                w.vi[col * w.ldv + row] = 0.0;
+        const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int nvt = nv <= 16 ? 1 : 2;
+        for (int col = wid; col < 16 * nvt; col += CT / 64) {
+            const int row = tid & 63;
+            if (row >= len || col >= nv) {          // zero-padded W (len <= 64)
+                w.wr[col * kLdsW + row] = 0.0;
+                w.wi[col * kLdsW + row] = 0.0;
             }
-            wave_sync();
-            int used = 0;
-            if (nv >= 2) {
+            if (row < nv && col < nv) {
+                w.vr[col * kLdsV + row] = row == col ? 1.0 : 0.0;
+                w.vi[col * kLdsV + row] = 0.0;
+            }
+        }
+        ldsd* W = to_lds(w.wr);
+        const int lp = static_cast<int>(w.wi - w.wr);
+        const double tol = 3e-15;
+        double floor2 = -1.0;
+        for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
+            if (tid < kWaveCols) J->cnt[tid] = 0;
+            if (tid == 0) J->over = 0;
+            __syncthreads();
+            f64x4 re, im;
+            if (wid < nvt) {
+                gram_tile(W, wid, wid, kLdsW, lp, len, re, im);
+                store_diagonal(re, (ldsd*)J->nrm + 16 * wid);
+            } else if (nvt == 2 && wid == 2) {
+                gram_tile(W, 0, 1, kLdsW, lp, len, re, im);
+            }
+            __syncthreads();
+            if (floor2 < 0.0) {
+                const int lane = tid & 63;
+                floor2 = 1e-2 * thr * thr * wave_sum(lane < 16 * nvt ? (double)J->nrm[lane] : 0.0);
+            }
+            int any = 0;
+            if (wid < nvt)
+                any = tile_overlaps<__HIP_MEMORY_SCOPE_WORKGROUP>(wid, wid, re, im, J, floor2, tol * tol);
+            else if (nvt == 2 && wid == 2)
+                any = tile_overlaps<__HIP_MEMORY_SCOPE_WORKGROUP>(0, 1, re, im, J, floor2, tol * tol);
+            if (any)
+                __hip_atomic_fetch_or(&J->over, any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __syncthreads();
+            const int over = J->over;
+            if (over == 0) return sweep + 1;
+            if (over < 2) {
+                // the pairs of tile t by the lanes of their lower columns
+                const int t = nvt == 1 ? 0 : wid & 1, part = nvt == 1 ? wid : wid >> 1;
+                const int v = 16 * t + (tid & 15);
+                const int u = J->cnt[v] ? (int)J->mate[v] : -1;
+                if (u > v) {
+                    const double gr = J->gre[v], gi = J->gim[v];
+                    const double d = J->nrm[u] - J->nrm[v];
+                    const double g2 = gr * gr + gi * gi;
+                    const double q1 = d * d + 4.0 * g2;
+                    const double D = fabs(d) + sqrt(q1);
+                    const double rq = 1.0 / sqrt(D * D + 4.0 * g2);
+                    const double sg = (d >= 0.0 ? 2.0 : -2.0) * rq;
+                    const double c = D * rq, ur = sg * gr, ui = sg * gi;
+                    const auto rot = [&](double* xr, double* xi, double* yr, double* yi, int n) {
+                        for (int r = 4 * part + ((tid >> 4) & 3); r < n; r += nvt == 1 ? 16 : 8) {
+                            const double x0 = xr[r], x1 = xi[r], y0 = yr[r], y1 = yi[r];
+                            xr[r] = c * x0 - (ur * y0 + ui * y1);
+                            xi[r] = c * x1 - (ur * y1 - ui * y0);
+                            yr[r] = c * y0 + (ur * x0 - ui * x1);
+                            yi[r] = c * y1 + (ur * x1 + ui * x0);
+                        }
+                    };
+                    rot(w.wr + v * kLdsW, w.wi + v * kLdsW, w.wr + u * kLdsW, w.wi + u * kLdsW, len);
+                    rot(w.vr + v * kLdsV, w.vi + v * kLdsV, w.vr + u * kLdsV, w.vi + u * kLdsV, nv);
+                }
+            } else if (tid < 64) {
                 const int m = nv + (nv & 1), np = m / 2;
                 int G = 64;
                 while (G > 1 && G * np > 64) G >>= 1;
                 const int g = tid / G, l = tid - g * G;
-                used = -1;
-                for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
-                    int rotated = 0;
-                    for (int t = 0; t < m - 1; ++t) {
-                        if (g < np) {
-                            int p, q;
-                            rr_pair(g, t, m, p, q);
-                            if (jacobi_pair(w, len, nv, p, q, G, l)) rotated = 1;
-                        }
-                        wave_sync();
+                for (int t = 0; t < m - 1; ++t) {
+                    if (g < np) {
+                        int p, q;
+                        rr_pair(g, t, m, p, q);
+                        jacobi_pair(w, len, nv, p, q, G, l);
                     }
-                    if (__ballot(rotated) == 0ull) {
-                        used = sweep + 1;
-                        break;
-                    }
+                    wave_sync();
                 }
             }
-            if (tid == 0) s_sw = used;
+            __syncthreads();
         }
-        __syncthreads();
-        const int used = s_sw;
-        __syncthreads();
-        return used;
+        return -1;
     }
     for (int e = tid; e < nv * nv; e += CT) {
         const int col = e / nv, row = e - col * nv;
@@ -268,8 +335,23 @@ __device__ int jacobi_cols(const WV& w, int len, int nv, int* s_flag) {
 // column norms of W (nv columns) into sg[], kept columns (sigma > tau *
 // sigma_max, in order) into keep[]; returns how many
 __device__ int select_cols(const WV& w, int len, int nv, double tau, double* sg, int* keep,
-                           double* red) {
+                           double* red, const LPair* J) {
     const int tid = threadIdx.x;
+    __shared__ int s_cnt;
+    if (w.wave) {
+        // wavefront 0, the norms from the last Gram matrix
+        if (tid < 64) {
+            const double x = tid < nv ? sqrt(J->nrm[tid]) : 0.0;
+            const double mx = wave_max(x);
+            const bool k = tid < nv && x > tau * mx && x > 0.0;
+            const uint64_t m = __ballot(k);
+            if (tid < nv) sg[tid] = x;
+            if (k) keep[__popcll(m & ((1ull << tid) - 1ull))] = tid;
+            if (tid == 0) s_cnt = __popcll(m);
+        }
+        __syncthreads();
+        return s_cnt;    // (rewritten only after the caller's next barrier)
+    }
     for (int col = tid; col < nv; col += CT) {
         double s = 0;
         for (int r = 0; r < len; ++r) {
@@ -283,7 +365,6 @@ __device__ int select_cols(const WV& w, int len, int nv, double tau, double* sg,
     double mx = 0;
     for (int col = tid; col < nv; col += CT) mx = fmax(mx, sg[col]);
     mx = block_max(mx, red);
-    __shared__ int s_cnt;
     if (tid == 0) {
         int r = 0;
         for (int col = 0; col < nv; ++col)
@@ -308,7 +389,8 @@ struct Ctl {
     int* sweeps;      // LDS: Jacobi sweeps
     int* chi_peak;    // LDS
     int* old;         // LDS [kMaxSites + 1]: bonds before apply_sum
-    double *lwr, *lwi, *lvr, *lvi;   // LDS work matrices of the wave SVDs
+    double *lwr, *lwi, *lvr, *lvi;   // LDS work matrices of the small SVDs
+    LPair* pairs;                    // their overlapping pairs
 };
 
 __device__ __forceinline__ WV work_mats(const Res& R, const Ctl& c, int len, int nv) {
@@ -318,8 +400,8 @@ __device__ __forceinline__ WV work_mats(const Res& R, const Ctl& c, int len, int
         w.wi = c.lwi;
         w.vr = c.lvr;
         w.vi = c.lvi;
-        w.ldw = kWaveLen;
-        w.ldv = kWaveCols;
+        w.ldw = kLdsW;
+        w.ldv = kLdsV;
         w.wave = true;
     } else {
         w.wr = R.scr + oW;
@@ -355,8 +437,8 @@ __device__ void move_right(const Res& R, const Ctl& c, int k, double tau) {
         wi[b * ldw + row] = ai[row * cr + b];
     }
     __syncthreads();
-    note_sweeps(c, jacobi_cols(w, len, cr, c.flag));
-    const int r = select_cols(w, len, cr, tau, c.sg, c.keep, c.red);
+    note_sweeps(c, jacobi_cols(w, len, cr, tau, c.flag, c.pairs));
+    const int r = select_cols(w, len, cr, tau, c.sg, c.keep, c.red, c.pairs);
     double *Ar = R.re(k), *Ai = R.im(k);
     for (int e = tid; e < len * r; e += CT) {
         const int row = e / r, j = e - row * r;
@@ -414,8 +496,8 @@ __device__ void move_left(const Res& R, const Ctl& c, int k, double tau) {
         wi[a * ldw + x] = -ai[a * len + x];
     }
     __syncthreads();
-    note_sweeps(c, jacobi_cols(w, len, cl, c.flag));
-    const int r = select_cols(w, len, cl, tau, c.sg, c.keep, c.red);
+    note_sweeps(c, jacobi_cols(w, len, cl, tau, c.flag, c.pairs));
+    const int r = select_cols(w, len, cl, tau, c.sg, c.keep, c.red, c.pairs);
     double *Ar = R.re(k), *Ai = R.im(k);
     for (int e = tid; e < r * len; e += CT) {
         const int j = e / len, x = e - j * len;
@@ -686,8 +768,8 @@ __device__ bool apply_sum(const Res& R, const Ctl& c, Frame F, int r, double alr
             __syncthreads();
             break;
         }
-        note_sweeps(c, jacobi_cols(w, len, D, c.flag));
-        const int rn = select_cols(w, len, D, 1e-14, c.sg, c.keep, c.red);
+        note_sweeps(c, jacobi_cols(w, len, D, 1e-14, c.flag, c.pairs));
+        const int rn = select_cols(w, len, D, 1e-14, c.sg, c.keep, c.red, c.pairs);
         if (rn > K) return false;     // cannot happen: rn <= D <= K
         double *Ar = R.re(k), *Ai = R.im(k);
         for (int e = tid; e < len * rn; e += CT) {
@@ -733,8 +815,8 @@ __global__ __launch_bounds__(CT) void camps_kernel(CampsArgs P) {
     __shared__ double s_pur[kCampsCand + 1];
     __shared__ double s_dm[(kCampsCand + 1) * 32];   // identity, then the candidates
     __shared__ double s_part[CT];
-    __shared__ double s_lwr[kWaveLen * kWaveCols], s_lwi[kWaveLen * kWaveCols];
-    __shared__ double s_lvr[kWaveCols * kWaveCols], s_lvi[kWaveCols * kWaveCols];
+    __shared__ double s_lw[2 * kLdsW * kWaveCols], s_lv[2 * kLdsV * kWaveCols];   // re, im
+    __shared__ PairLds s_pairs;
     const int tid = threadIdx.x;
     const int n = P.n;
     Frame F;
@@ -753,10 +835,11 @@ __global__ __launch_bounds__(CT) void camps_kernel(CampsArgs P) {
     C.sweeps = &s_sweeps;
     C.chi_peak = &s_peak;
     C.old = s_old;
-    C.lwr = s_lwr;
-    C.lwi = s_lwi;
-    C.lvr = s_lvr;
-    C.lvi = s_lvi;
+    C.lwr = s_lw;
+    C.lwi = s_lw + kLdsW * kWaveCols;
+    C.lvr = s_lv;
+    C.lvi = s_lv + kLdsV * kWaveCols;
+    C.pairs = (LPair*)&s_pairs;
     const double c8 = 0.92387953251128675613, s8 = 0.38268343236508977173;   // cos, sin of pi/8
     for (int e = tid; e < (kCampsCand + 1) * 32; e += CT) {
         const int c = e / 32, w = e - c * 32;
@@ -1026,8 +1109,8 @@ __global__ __launch_bounds__(CT) void camps_kernel(CampsArgs P) {
                 }
                 __syncthreads();
                 // split D theta: A_k = U, A_{k+1} = S V^dag
-                note_sweeps(C, jacobi_cols(w, m, nn, &s_flag));
-                const int rr = select_cols(w, m, nn, tau, s_sg, s_keep, s_red);
+                note_sweeps(C, jacobi_cols(w, m, nn, tau, &s_flag, C.pairs));
+                const int rr = select_cols(w, m, nn, tau, s_sg, s_keep, s_red, C.pairs);
                 double *Ar = R.re(k), *Ai = R.im(k), *Br = R.re(k + 1), *Bi = R.im(k + 1);
                 for (int e = tid; e < m * rr; e += CT) {
                     const int row = e / rr, jj = e - row * rr;
