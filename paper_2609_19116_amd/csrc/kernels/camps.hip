@@ -812,9 +812,11 @@ __global__ __launch_bounds__(CT) void camps_kernel(CampsArgs P) {
     __shared__ double s_sg[K];
     __shared__ int s_keep[K];
     __shared__ int s_flag, s_center, s_status, s_sweeps, s_peak, s_best;
-    __shared__ double s_pur[kCampsCand + 1];
     __shared__ double s_dm[(kCampsCand + 1) * 32];   // identity, then the candidates
-    __shared__ double s_part[CT];
+    __shared__ double s_part[CT / 64 * 16];
+    // per side and candidate (0: none) the four Paulis (z 4 + x on in = 2 i + j)
+    // that it maps to the identity on the other site's leg
+    __shared__ uint8_t s_set[2 * (kCampsCand + 1) * 4];
     __shared__ double s_lw[2 * kLdsW * kWaveCols], s_lv[2 * kLdsV * kWaveCols];   // re, im
     __shared__ PairLds s_pairs;
     const int tid = threadIdx.x;
@@ -844,6 +846,16 @@ __global__ __launch_bounds__(CT) void camps_kernel(CampsArgs P) {
     for (int e = tid; e < (kCampsCand + 1) * 32; e += CT) {
         const int c = e / 32, w = e - c * 32;
         s_dm[e] = c == 0 ? ((w % 2 == 0 && (w / 2) % 5 == 0) ? 1.0 : 0.0) : P.dmat[(c - 1) * 32 + w];
+    }
+    if (tid < 2 * (kCampsCand + 1)) {
+        const int right = tid / (kCampsCand + 1), c = tid - right * (kCampsCand + 1);
+        int h = 0;
+        for (int code = 0; code < 16; ++code) {    // x1 z1 x2 z2 of sites k, k + 1
+            const int t = c == 0 ? code : P.dtab[(c - 1) * 16 + code] & 15;
+            if ((right ? t & 3 : t >> 2) || h >= 4) continue;
+            const int x = 2 * (code & 1) + ((code >> 2) & 1), z = (code & 2) + ((code >> 3) & 1);
+            s_set[tid * 4 + h++] = static_cast<uint8_t>(4 * z + x);
+        }
     }
     __syncthreads();
 
@@ -997,73 +1009,60 @@ __global__ __launch_bounds__(CT) void camps_kernel(CampsArgs P) {
                     gi[e] = xi;
                 }
                 __syncthreads();
-                // purity of every candidate (0 = no gate), kCampsCand + 1 teams
-                // of 12 threads, each summing |rho|^2 over a fixed stride
-                constexpr int TPC = CT / (kCampsCand + 1);
-                const int cand = tid / TPC, lane = tid - cand * TPC;
-                double part = 0.0;
-                if (cand <= kCampsCand) {
-                    const double* d = s_dm + cand * 32;
-                    const int rd = left ? m : nn;           // rho is rd x rd
-                    for (int e = lane; e < rd * rd; e += TPC) {
-                        const int x1 = e / rd, x2 = e - x1 * rd;
-                        double rr = 0, ri = 0;
-                        if (left) {
-                            const int a = x1 >> 1, ip = x1 & 1, a2 = x2 >> 1, i2p = x2 & 1;
-                            for (int jp = 0; jp < 2; ++jp)
-                                for (int in = 0; in < 4; ++in) {
-                                    const int o1 = (2 * ip + jp) * 4 + in;
-                                    const double d1r = d[2 * o1], d1i = d[2 * o1 + 1];
-                                    if (d1r == 0.0 && d1i == 0.0) continue;
-                                    for (int in2 = 0; in2 < 4; ++in2) {
-                                        const int o2 = (2 * i2p + jp) * 4 + in2;
-                                        const double d2r = d[2 * o2], d2i = -d[2 * o2 + 1];
-                                        if (d2r == 0.0 && d2i == 0.0) continue;
-                                        const int g = (a * 4 + in) * gd + (a2 * 4 + in2);
-                                        // d1 * conj(d2') * G
-                                        const double pr_ = d1r * d2r - d1i * d2i, pi_ = d1r * d2i + d1i * d2r;
-                                        rr += pr_ * gr[g] - pi_ * gi[g];
-                                        ri += pr_ * gi[g] + pi_ * gr[g];
-                                    }
-                                }
-                        } else {
-                            const int jp = x1 / cr, b = x1 - jp * cr, j2p = x2 / cr, b2 = x2 - j2p * cr;
-                            for (int ip = 0; ip < 2; ++ip)
-                                for (int in = 0; in < 4; ++in) {
-                                    const int o1 = (2 * ip + jp) * 4 + in;
-                                    const double d1r = d[2 * o1], d1i = -d[2 * o1 + 1];   // conj
-                                    if (d1r == 0.0 && d1i == 0.0) continue;
-                                    for (int in2 = 0; in2 < 4; ++in2) {
-                                        const int o2 = (2 * ip + j2p) * 4 + in2;
-                                        const double d2r = d[2 * o2], d2i = d[2 * o2 + 1];
-                                        if (d2r == 0.0 && d2i == 0.0) continue;
-                                        const int g = (in * cr + b) * gd + (in2 * cr + b2);
-                                        const double pr_ = d1r * d2r - d1i * d2i, pi_ = d1r * d2i + d1i * d2r;
-                                        rr += pr_ * gr[g] - pi_ * gi[g];
-                                        ri += pr_ * gi[g] + pi_ * gr[g];
-                                    }
-                                }
-                        }
-                        part += rr * rr + ri * ri;
+                // Purity of every candidate.  With g_P[a, a2] = tr(P^dag G[a, a2])
+                // over the 16 two-qubit Paulis P of the legs (i, j), D G D^dag has
+                // the coefficient +-g_P at the Pauli D P D^dag, and the trace over
+                // the other site's leg keeps the four that act as the identity
+                // there: tr(rho_D^2) = 1/2 sum over those P of |g_P|^2, 16 norms
+                // for all candidates.  (Summing rho_D itself took 3.1e4 cycles a
+                // bond, most of the disentangler; now @@.)
+                double nz[4] = {0.0, 0.0, 0.0, 0.0};
+                const int px = tid & 3;                 // x bits of P on in = 2 i + j
+                for (int e = tid >> 2; e < sd * sd; e += CT / 4) {
+                    const int u = e / sd, v = e - u * sd;
+                    double vr4[4], vi4[4];
+#pragma unroll
+                    for (int in = 0; in < 4; ++in) {
+                        const int i1 = in ^ px;
+                        const int ge = left ? (u * 4 + i1) * gd + v * 4 + in
+                                            : (i1 * sd + u) * gd + in * sd + v;
+                        vr4[in] = gr[ge];
+                        vi4[in] = gi[ge];
                     }
-                    s_part[tid] = part;
+                    // signs (-1)^(z . in): z = 0, j's, i's, both
+                    const double ar0 = vr4[0] + vr4[1], ar1 = vr4[0] - vr4[1];
+                    const double br0 = vr4[2] + vr4[3], br1 = vr4[2] - vr4[3];
+                    const double ai0 = vi4[0] + vi4[1], ai1 = vi4[0] - vi4[1];
+                    const double bi0 = vi4[2] + vi4[3], bi1 = vi4[2] - vi4[3];
+                    nz[0] += (ar0 + br0) * (ar0 + br0) + (ai0 + bi0) * (ai0 + bi0);
+                    nz[1] += (ar1 + br1) * (ar1 + br1) + (ai1 + bi1) * (ai1 + bi1);
+                    nz[2] += (ar0 - br0) * (ar0 - br0) + (ai0 - bi0) * (ai0 - bi0);
+                    nz[3] += (ar1 - br1) * (ar1 - br1) + (ai1 - bi1) * (ai1 - bi1);
+                }
+#pragma unroll
+                for (int z = 0; z < 4; ++z) {
+#pragma unroll
+                    for (int o = 4; o < 64; o <<= 1) nz[z] += __shfl_xor(nz[z], o);
+                    if ((tid & 63) < 4) s_part[(tid >> 6) * 16 + 4 * z + px] = nz[z];
                 }
                 __syncthreads();
-                if (tid <= kCampsCand) {
-                    double acc = 0.0;
-                    for (int l = 0; l < TPC; ++l) acc += s_part[tid * TPC + l];
-                    s_pur[tid] = acc;
-                }
-                __syncthreads();
-                if (tid == 0) {
-                    double best = s_pur[0];
+                if (tid < 64) {
+                    double pur = 0.0;
+                    if (tid <= kCampsCand)
+                        for (int h = 0; h < 4; ++h) {
+                            const int p = s_set[((left ? 0 : 1) * (kCampsCand + 1) + tid) * 4 + h];
+                            for (int w = 0; w < CT / 64; ++w) pur += s_part[16 * w + p];
+                        }
+                    double best = lane_read(pur, 0);
                     int choice = -1;
-                    for (int cc = 0; cc < kCampsCand; ++cc)
-                        if (s_pur[cc + 1] > best * (1.0 + 1e-9)) {
-                            best = s_pur[cc + 1];
+                    for (int cc = 0; cc < kCampsCand; ++cc) {
+                        const double x = lane_read(pur, cc + 1);
+                        if (x > best * (1.0 + 1e-9)) {
+                            best = x;
                             choice = cc;
                         }
-                    s_best = choice;
+                    }
+                    if (tid == 0) s_best = choice;
                 }
                 __syncthreads();
                 const int choice = s_best;
