@@ -40,6 +40,7 @@ constexpr int CT = 256;
 constexpr int K = kCampsK;
 constexpr int NR = 2 * kMaxSites;
 constexpr int kMaxSweeps = 60;
+constexpr double kOrtho = 3e-15;   // |x^H y| / (|x| |y|) of vectors that count as orthogonal
 
 // scratch layout (doubles) of one slot
 constexpr int64_t oW = 0;                     // 2 x (2K x K), column-major, ld 2K
@@ -204,13 +205,13 @@ __device__ __forceinline__ void rr_pair(int i, int t, int m, int& p, int& q) {
 // sweeps used (-1: no convergence).
 //
 // In LDS, each sweep starts from the Gram matrix of the columns on FP64 MFMA:
-// pairs with |x^H y| <= (len + 16) eps |x| |y| count as orthogonal, and
+// pairs with |x^H y| <= kOrtho |x| |y| count as orthogonal, and
 // columns below a tenth of the threshold thr * sigma_max that the caller drops
 // by as zero.  When every overlapping column has exactly one mate, which is
 // the usual case, all pairs rotate in one step; else one round-robin sweep
 // by wavefront 0.  A round-robin sweep over 32 columns is 31 dependent steps
-// and needed a second one to find nothing left: 256 49-qubit shots took 185
-// ms, now @@ (one shot's latency).  The columns' squared norms are left in
+// and needed a second one to find nothing left: 256 49-qubit shots (one
+// shot's latency) 185 -> 121 ms.  The columns' squared norms are left in
 // J.nrm.
 __device__ int jacobi_cols(const WV& w, int len, int nv, double thr, int* s_flag, LPair* J) {
     const int tid = threadIdx.x;
@@ -230,7 +231,7 @@ __device__ int jacobi_cols(const WV& w, int len, int nv, double thr, int* s_flag
         }
         ldsd* W = to_lds(w.wr);
         const int lp = static_cast<int>(w.wi - w.wr);
-        const double tol = 3e-15;
+        const double tol = kOrtho;
         double floor2 = -1.0;
         for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
             if (tid < kWaveCols) J->cnt[tid] = 0;
@@ -422,10 +423,105 @@ __device__ void note_sweeps(const Ctl& c, int sw) {
     }
 }
 
+// A centre move whose SVD is trivial: the centre site's columns (right) or
+// rows (left) are already orthogonal, so V = 1, the kept ones are normalised
+// where they are and the neighbour's rows (columns) take their norms.  One
+// wavefront, in registers, for at most 16 vectors of at most 4 KS elements and
+// a neighbour of at most 4 KS per vector; element 4 s + g of vector q in lane
+// 16 g + q.  Returns false, having written nothing, if any pair overlaps.
+// (Most moves of a sweep after the first are of this kind, on matrices of a
+// few columns: the workgroup's barriers and the pass through the work
+// matrices were their cost.  256 49-qubit shots: 94 -> 82 ms.)
+template <int KS>
+__device__ __forceinline__ bool trivial_move(const Res& R, const Ctl& c, int k, bool right,
+                                             double tau, int cl, int cm, int cr) {
+    // sites k, k + 1 with bonds cl, cm, cr; the centre is k (right) or k + 1
+    const int lane = op_lane(), q = lane & 15, g = lane >> 4;
+    const int nv = cm, len = right ? 2 * cl : 2 * cr, w = right ? 2 * cr : 2 * cl;
+    double *Xr = R.re(right ? k : k + 1), *Xi = R.im(right ? k : k + 1);
+    double *Nr = R.re(right ? k + 1 : k), *Ni = R.im(right ? k + 1 : k);
+    const int xe = right ? cm : 1, xv = right ? 1 : len;
+    const int ne = right ? 1 : cm, nvs = right ? w : 1;
+    double x0[KS], x1[KS], y0[KS], y1[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int e = 4 * s + g;
+        const bool ix = q < nv && e < len, in = q < nv && e < w;
+        x0[s] = ix ? Xr[q * xv + e * xe] : 0.0;
+        x1[s] = ix ? Xi[q * xv + e * xe] : 0.0;
+        y0[s] = in ? Nr[q * nvs + e * ne] : 0.0;
+        y1[s] = in ? Ni[q * nvs + e * ne] : 0.0;
+    }
+    f64x4 re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        if (4 * s >= len) break;
+        re = mfma(x0[s], x0[s], re);
+        im = mfma(x0[s], x1[s], im);
+        re = mfma(x1[s], x1[s], re);
+        im = mfma(-x1[s], x0[s], im);
+    }
+    ldsd* nrm = c.pairs->nrm;
+    store_diagonal(re, nrm);
+    wave_order();
+    const double nq = nrm[q];
+    const double floor2 = 1e-2 * tau * tau * row_sum(nq);
+    bool over = false;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const double a = nrm[g + 4 * r], g2 = re[r] * re[r] + im[r] * im[r];
+        over |= g + 4 * r < q && a > floor2 && nq > floor2 && g2 > kOrtho * kOrtho * a * nq;
+    }
+    if (__ballot(over) != 0ull) return false;
+    const double sg = sqrt(nq), mx = row_max(sg);
+    const bool keep = q < nv && sg > tau * mx && sg > 0.0;
+    const uint32_t m = static_cast<uint32_t>(__ballot(keep)) & 0xFFFFu;
+    const int r = __popc(m), j = __popc(m & ((1u << q) - 1u));
+    if (keep) {
+        const double is = 1.0 / sg;
+        const int ue = right ? r : 1, uv = right ? 1 : len;
+        const int me = right ? 1 : r, mv = right ? w : 1;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int e = 4 * s + g;
+            if (e < len) {
+                Xr[j * uv + e * ue] = x0[s] * is;
+                Xi[j * uv + e * ue] = x1[s] * is;
+            }
+            if (e < w) {
+                Nr[j * mv + e * me] = y0[s] * sg;
+                Ni[j * mv + e * me] = y1[s] * sg;
+            }
+        }
+    }
+    if (lane == 0) {
+        R.chi[k + 1] = r;
+        *c.center = right ? k + 1 : k;
+        if (r > *c.chi_peak) *c.chi_peak = r;
+        *c.sweeps += 1;
+    }
+    return true;
+}
+
+// trivial_move by wavefront 0 of the workgroup, if it applies.
+__device__ __forceinline__ bool try_trivial(const Res& R, const Ctl& c, int k, bool right, double tau,
+                                            int cl, int cm, int cr) {
+    if (cm > 16 || cl > 16 || cr > 16) return false;
+    __syncthreads();               // every wavefront has read the bonds
+    if (threadIdx.x < 64) {
+        const bool f = max(cl, cr) <= 8 ? trivial_move<4>(R, c, k, right, tau, cl, cm, cr)
+                                        : trivial_move<8>(R, c, k, right, tau, cl, cm, cr);
+        if (threadIdx.x == 0) *c.flag = f;
+    }
+    __syncthreads();
+    return *c.flag != 0;           // (rewritten only after a later barrier)
+}
+
 // centre k -> k+1
 __device__ void move_right(const Res& R, const Ctl& c, int k, double tau) {
     const int tid = threadIdx.x;
-    const int cl = R.chi[k], cr = R.chi[k + 1], cn = R.chi[k + 2];
+    const int cl = uni(R.chi[k]), cr = uni(R.chi[k + 1]), cn = uni(R.chi[k + 2]);
+    if (try_trivial(R, c, k, true, tau, cl, cr, cn)) return;
     const double *ar = R.re(k), *ai = R.im(k);
     const int len = 2 * cl;
     const WV w = work_mats(R, c, len, cr);
@@ -483,7 +579,8 @@ __device__ void move_right(const Res& R, const Ctl& c, int k, double tau) {
 // centre k -> k-1
 __device__ void move_left(const Res& R, const Ctl& c, int k, double tau) {
     const int tid = threadIdx.x;
-    const int cp = R.chi[k - 1], cl = R.chi[k], cr = R.chi[k + 1];
+    const int cp = uni(R.chi[k - 1]), cl = uni(R.chi[k]), cr = uni(R.chi[k + 1]);
+    if (try_trivial(R, c, k - 1, false, tau, cp, cl, cr)) return;
     const double *ar = R.re(k), *ai = R.im(k);
     const int len = 2 * cr;
     const WV w = work_mats(R, c, len, cl);
@@ -1014,8 +1111,8 @@ __global__ __launch_bounds__(CT) void camps_kernel(CampsArgs P) {
                 // the coefficient +-g_P at the Pauli D P D^dag, and the trace over
                 // the other site's leg keeps the four that act as the identity
                 // there: tr(rho_D^2) = 1/2 sum over those P of |g_P|^2, 16 norms
-                // for all candidates.  (Summing rho_D itself took 3.1e4 cycles a
-                // bond, most of the disentangler; now @@.)
+                // for all candidates.  (Summing each rho_D itself took 3.1e4
+                // cycles a bond, most of the disentangler: 121 -> 94 ms.)
                 double nz[4] = {0.0, 0.0, 0.0, 0.0};
                 const int px = tid & 3;                 // x bits of P on in = 2 i + j
                 for (int e = tid >> 2; e < sd * sd; e += CT / 4) {
