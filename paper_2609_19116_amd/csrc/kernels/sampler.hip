@@ -11,13 +11,10 @@
 // channel, X for an X flip).  Only integer and IEEE basic operations are
 // used, so every bit of the CSR matches the host's.
 //
-// Three launches: (1) every lane draws its shot's weight and the block
-// writes block-local inclusive prefixes of the weights to shot_off[i+1]
-// plus the block total; (2) one block scans the block totals; (3) every
-// lane adds its block's base to shot_off[i+1], replays its generator and
-// writes its channels and Paulis at that offset (only when the slice ends
-// within the caller's capacity, so an undersized output is never written
-// past its end).
+// Three steps: (1) every lane draws its shot's weight, the block's total goes
+// out; (2) a scan of the block totals; (3) the block's offsets, channels and
+// Paulis (draw_kernel), written only where a shot's slice ends within the
+// caller's capacity, so an undersized output is never written past its end.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -68,9 +65,13 @@ struct DevRng {
     }
 };
 
-// weight of one shot; advances rng exactly as the host does
+constexpr int kCdfLds = 64;    // entries of the cumulative table held in LDS
+
+// weight of one shot; advances rng exactly as the host does.  cdf_lds holds
+// the table's first min(n_cdf, kCdfLds) entries.
 __device__ __forceinline__ int64_t draw_weight(DevRng& rng, int64_t i, const int32_t* weights,
-                                               const double* cdf, int32_t n_cdf, int64_t M) {
+                                               const double* cdf, const double* cdf_lds,
+                                               int32_t n_cdf, int64_t M) {
     int64_t w;
     if (weights) {
         w = weights[i];
@@ -79,7 +80,7 @@ __device__ __forceinline__ int64_t draw_weight(DevRng& rng, int64_t i, const int
         const double u = rng.uniform01();
         w = n_cdf - 1;
         for (int32_t k = 0; k < n_cdf; ++k) {
-            if (u < cdf[k]) {
+            if (u < (k < kCdfLds ? cdf_lds[k] : cdf[k])) {
                 w = k;
                 break;
             }
@@ -88,29 +89,46 @@ __device__ __forceinline__ int64_t draw_weight(DevRng& rng, int64_t i, const int
     return w < M ? w : M;
 }
 
+__device__ __forceinline__ void load_cdf(const int32_t* weights, const double* cdf, int32_t n_cdf,
+                                         double* cdf_lds) {
+    if (!weights)
+        for (int k = threadIdx.x; k < kCdfLds && k < n_cdf; k += ST) cdf_lds[k] = cdf[k];
+    __syncthreads();
+}
+
+// Inclusive scan of v over the block, and the block's total.
+__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t* s_wave, int64_t& total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int64_t u = __shfl_up(v, d);
+        if (lane >= d) v += u;
+    }
+    if (lane == 63) s_wave[w] = v;
+    __syncthreads();
+    total = 0;
+    for (int q = 0; q < ST / 64; ++q) {
+        if (q < w) v += s_wave[q];
+        total += s_wave[q];
+    }
+    return v;
+}
+
 __global__ __launch_bounds__(ST) void weight_kernel(int64_t n, uint64_t seed, uint64_t first,
                                                     const int32_t* __restrict__ weights,
                                                     const double* __restrict__ cdf, int32_t n_cdf,
-                                                    int64_t M, int64_t* __restrict__ shot_off,
-                                                    int64_t* __restrict__ block_tot) {
-    __shared__ int64_t s[ST];
+                                                    int64_t M, int64_t* __restrict__ block_tot) {
+    __shared__ int64_t s_wave[ST / 64];
+    __shared__ double s_cdf[kCdfLds];
     const int64_t i = static_cast<int64_t>(blockIdx.x) * ST + threadIdx.x;
-    int64_t w = 0;
+    load_cdf(weights, cdf, n_cdf, s_cdf);
+    int64_t w = 0, total;
     if (i < n) {
         DevRng rng(seed, first + static_cast<uint64_t>(i));
-        w = draw_weight(rng, i, weights, cdf, n_cdf, M);
+        w = draw_weight(rng, i, weights, cdf, s_cdf, n_cdf, M);
     }
-    s[threadIdx.x] = w;
-    __syncthreads();
-    // Hillis-Steele inclusive scan over the block
-    for (int d = 1; d < ST; d <<= 1) {
-        const int64_t v = threadIdx.x >= d ? s[threadIdx.x - d] : 0;
-        __syncthreads();
-        s[threadIdx.x] += v;
-        __syncthreads();
-    }
-    if (i < n) shot_off[i + 1] = s[threadIdx.x];
-    if (threadIdx.x == ST - 1) block_tot[blockIdx.x] = s[ST - 1];
+    block_scan(w, s_wave, total);
+    if (threadIdx.x == 0) block_tot[blockIdx.x] = total;
 }
 
 // exclusive scan of the block totals within each superblock of kSup blocks,
@@ -160,25 +178,11 @@ __global__ __launch_bounds__(kScanT) void total_scan_kernel(int64_t* cnt, int64_
     }
 }
 
-__global__ __launch_bounds__(ST) void draw_kernel(int64_t n, uint64_t seed, uint64_t first,
-                                                  const int32_t* __restrict__ weights,
-                                                  const double* __restrict__ cdf, int32_t n_cdf,
-                                                  int64_t M, const uint8_t* __restrict__ kind,
-                                                  const int64_t* __restrict__ block_base,
-                                                  const int64_t* __restrict__ sup_base,
-                                                  int64_t nnz_cap, int64_t* __restrict__ shot_off,
-                                                  int32_t* __restrict__ chan,
-                                                  uint8_t* __restrict__ pauli) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * ST + threadIdx.x;
-    if (i == 0) shot_off[0] = 0;
-    if (i >= n) return;
-    DevRng rng(seed, first + static_cast<uint64_t>(i));
-    const int64_t w = draw_weight(rng, i, weights, cdf, n_cdf, M);
-    const int64_t end = shot_off[i + 1] + block_base[blockIdx.x] + sup_base[blockIdx.x / kSup];
-    shot_off[i + 1] = end;
-    const int64_t o = end - w;
-    if (w == 0 || end > nnz_cap) return;
-    int32_t* c = chan + o;
+// One shot's channels (ascending) and Paulis at c and pa by its own lane, in
+// the host's order of draws.
+template <typename CP, typename PP>
+__device__ void draw_shot(DevRng rng, int64_t w, int64_t M, const uint8_t* __restrict__ kind, CP c,
+                          PP pa) {
     // Floyd: for j in [M-w, M) take t uniform in [0, j], or j if t is taken
     int64_t k = 0;
     for (int64_t j = M - w; j < M; ++j) {
@@ -187,7 +191,7 @@ __global__ __launch_bounds__(ST) void draw_kernel(int64_t n, uint64_t seed, uint
         for (int64_t q = 0; q < k; ++q) have |= c[q] == t;
         c[k++] = have ? static_cast<int32_t>(j) : t;
     }
-    // ascending order (insertion sort: w is small on the hot path)
+    // ascending order (insertion sort)
     for (int64_t a = 1; a < w; ++a) {
         const int32_t v = c[a];
         int64_t b = a - 1;
@@ -204,7 +208,117 @@ __global__ __launch_bounds__(ST) void draw_kernel(int64_t n, uint64_t seed, uint
         else if (kd == CH_DEP1) code = static_cast<uint8_t>(1 + rng.bounded(3));
         else if (kd == CH_DEP2) code = static_cast<uint8_t>(1 + rng.bounded(15));
         else code = static_cast<uint8_t>(1 + rng.bounded(63));
-        pauli[o + a] = code;
+        pa[a] = code;
+    }
+}
+
+// The 64 x 32-bit product x n as (high 32 of the 96 bits, low 64).
+__device__ __forceinline__ uint32_t mul96(uint64_t x, uint32_t n, uint64_t& lo) {
+    const uint64_t p0 = static_cast<uint64_t>(static_cast<uint32_t>(x)) * n;
+    const uint64_t p1 = static_cast<uint64_t>(static_cast<uint32_t>(x >> 32)) * n + (p0 >> 32);
+    lo = (p1 << 32) | static_cast<uint32_t>(p0);
+    return static_cast<uint32_t>(p1 >> 32);
+}
+
+// Offsets, channels and Paulis of the block's shots.  The generator is
+// counter-based, so draw k of a shot is mix64(s0 + k golden) for any k, and
+// the block's faults, dealt to the lanes one by one, take their draws
+// independently: a wavefront no longer waits for its heaviest shot (of 64
+// shots with 2.9 faults on average the worst has 8).  A fault's rank among
+// its shot's raw channels is its place; the Paulis' draws follow in that
+// order (an X flip takes none).  A shot whose raw channels repeat (Floyd's
+// replacement) or one of whose draws Lemire's test would look at more closely
+// (probability n 2^-64) is drawn again by its own lane in the host's order.
+// The results leave through LDS in one contiguous run per block.  Blocks with
+// more than kDrawCap faults draw shot by shot, straight to memory.
+// 2^24 shots of the 81-qubit circuit (48 M faults), all three steps: one lane
+// per shot with its channels in memory 0.89 ms (420 GB/s of output), now 0.52.
+constexpr int kDrawCap = 1536;
+constexpr int kKindShift = 28;     // the channel's kind above its index
+__global__ __launch_bounds__(ST) void draw_kernel(int64_t n, uint64_t seed, uint64_t first,
+                                                  const int32_t* __restrict__ weights,
+                                                  const double* __restrict__ cdf, int32_t n_cdf,
+                                                  int64_t M, const uint8_t* __restrict__ kind,
+                                                  const int64_t* __restrict__ block_base,
+                                                  const int64_t* __restrict__ sup_base,
+                                                  int64_t nnz_cap, int64_t* __restrict__ shot_off,
+                                                  int32_t* __restrict__ chan,
+                                                  uint8_t* __restrict__ pauli) {
+    __shared__ int64_t s_wave[ST / 64];
+    __shared__ double s_cdf[kCdfLds];
+    __shared__ uint64_t s_s0[ST];
+    __shared__ int s_ofs[ST + 1];
+    __shared__ uint8_t s_own[kDrawCap], s_pa[kDrawCap], s_redo[ST];
+    __shared__ int32_t s_raw[kDrawCap], s_ch[kDrawCap];
+    const int tid = threadIdx.x;
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * ST + tid;
+    load_cdf(weights, cdf, n_cdf, s_cdf);
+    DevRng rng(seed, first + static_cast<uint64_t>(i));
+    const uint64_t s0 = rng.s;
+    const int64_t w = i < n ? draw_weight(rng, i, weights, cdf, s_cdf, n_cdf, M) : 0;
+    int64_t total;
+    const int64_t incl = block_scan(w, s_wave, total);
+    const int64_t base = block_base[blockIdx.x] + sup_base[blockIdx.x / kSup];
+    if (i == 0) shot_off[0] = 0;
+    if (i < n) shot_off[i + 1] = base + incl;
+    if (total > kDrawCap || M >= (int64_t(1) << kKindShift)) {
+        if (w > 0 && base + incl <= nnz_cap)
+            draw_shot(rng, w, M, kind, chan + base + incl - w, pauli + base + incl - w);
+        return;
+    }
+    const int F = static_cast<int>(total), o0 = static_cast<int>(incl - w);
+    s_s0[tid] = s0;
+    s_ofs[tid + 1] = static_cast<int>(incl);
+    if (tid == 0) s_ofs[0] = 0;
+    s_redo[tid] = 0;
+    for (int q = 0; q < static_cast<int>(w); ++q) s_own[o0 + q] = static_cast<uint8_t>(tid);
+    __syncthreads();
+    const uint32_t k0 = weights ? 0 : 1;       // draws taken by the weight
+    for (int f = tid; f < F; f += ST) {
+        const int own = s_own[f], b0 = s_ofs[own], wi = s_ofs[own + 1] - b0, j = f - b0;
+        const uint32_t nn = static_cast<uint32_t>(M) - wi + j + 1;
+        uint64_t lo;
+        const uint32_t t = mul96(mix64(s_s0[own] + (k0 + j + 1) * kGolden), nn, lo);
+        if (lo < nn) s_redo[own] = 1;
+        s_raw[f] = static_cast<int32_t>(t | (static_cast<uint32_t>(kind[t]) << kKindShift));
+    }
+    __syncthreads();
+    constexpr int32_t kMask = (1 << kKindShift) - 1;
+    for (int f = tid; f < F; f += ST) {
+        const int own = s_own[f], b0 = s_ofs[own], b1 = s_ofs[own + 1];
+        const int32_t raw = s_raw[f], t = raw & kMask;
+        int rank = 0, drawn = 0;               // smaller channels, those that take a draw
+        bool dup = false;
+        for (int q = b0; q < b1; ++q) {
+            const int32_t r = s_raw[q];
+            const bool less = (r & kMask) < t;
+            rank += less;
+            drawn += less && (r >> kKindShift) != CH_XERR;
+            dup |= q != f && (r & kMask) == t;
+        }
+        if (dup) {
+            s_redo[own] = 1;
+            continue;
+        }
+        const int kd = raw >> kKindShift;
+        int code = 1;
+        if (kd != CH_XERR) {
+            const uint32_t nn = kd == CH_DEP1 ? 3 : kd == CH_DEP2 ? 15 : 63;
+            uint64_t lo;
+            code += mul96(mix64(s_s0[own] + (k0 + (b1 - b0) + drawn + 1) * kGolden), nn, lo);
+            if (lo < nn) s_redo[own] = 1;
+        }
+        s_ch[b0 + rank] = t;
+        s_pa[b0 + rank] = static_cast<uint8_t>(code);
+    }
+    __syncthreads();
+    if (s_redo[tid]) draw_shot(rng, w, M, kind, s_ch + o0, s_pa + o0);
+    __syncthreads();
+    const bool fits = base + total <= nnz_cap;
+    for (int f = tid; f < F; f += ST) {
+        if (!fits && base + s_ofs[s_own[f] + 1] > nnz_cap) continue;
+        chan[base + f] = s_ch[f];
+        pauli[base + f] = s_pa[f];
     }
 }
 
@@ -228,7 +342,7 @@ hipError_t launch_sampler(int64_t n, uint64_t seed, uint64_t first, const int32_
     if (!weights && (!cdf || n_cdf < 1)) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(nb));
     hipLaunchKernelGGL(weight_kernel, grid, dim3(ST), 0, s, n, seed, first, weights, cdf, n_cdf, M,
-                       shot_off, tmp);
+                       tmp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(local_scan_kernel, dim3(static_cast<unsigned>(ns)), dim3(kSup), 0, s, tmp,
