@@ -239,7 +239,7 @@ static void free_device(msc_circuit* c) {
     free_camps_prefix(c->camps_prefix);
     if (c->dev < 0) return;
     (void)hipSetDevice(c->dev);
-    for (void** p : {&c->d_ops, &c->d_g1, &c->d_g4, &c->d_sig, &c->d_sig_off, &c->d_expected, &c->d_kind,
+    for (void** p : {&c->d_ops, &c->d_g1, &c->d_g4, &c->d_sig, &c->d_sig_off, &c->d_hash, &c->d_expected, &c->d_kind,
                      &c->d_segm, &c->d_camps_ops, &c->d_chan_q, &c->d_site_of, &c->d_dmat,
                      &c->d_dtab}) {
         if (*p) (void)hipFree(*p);
@@ -297,6 +297,36 @@ static int upload(msc_ctx* ctx, msc_circuit* c) {
         }
         if ((rc = put(&c->d_sig, comb.data(), comb.size() * sizeof(uint64_t)))) return rc;
         if ((rc = put(&c->d_sig_off, soff.data(), soff.size() * sizeof(int32_t)))) return rc;
+        // its first look: per (channel, code) a linear hash of the signature,
+        // the XOR of a fixed random 63-bit word per signature bit, at a fixed
+        // stride; the top bit marks codes the channel does not have
+        c->hash_shift = 4;
+        for (int32_t k : c->chan_kind)
+            if (k == CH_DEP3) c->hash_shift = 6;
+        const size_t entries = static_cast<size_t>(c->n_channels) << c->hash_shift;
+        if (entries <= kMaxHashEntries) {
+            std::vector<uint64_t> word(static_cast<size_t>(64) * W), hash(entries, kHashInvalid);
+            uint64_t st = 0x7363726565ull;
+            for (uint64_t& x : word) {      // SplitMix64
+                uint64_t z = (st += 0x9E3779B97F4A7C15ull);
+                z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+                z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+                x = (z ^ (z >> 31)) & ~kHashInvalid;
+            }
+            for (int ch = 0; ch < c->n_channels; ++ch) {
+                const size_t e0 = static_cast<size_t>(soff[ch] >> 2);
+                const size_t e1 = ch + 1 < c->n_channels ? static_cast<size_t>(soff[ch + 1] >> 2)
+                                                         : comb.size() / std::max(1, W);
+                for (size_t p = 1; p < e1 - e0; ++p) {
+                    uint64_t h = 0;
+                    for (int w = 0; w < W; ++w)
+                        for (uint64_t m = comb[(e0 + p) * W + w]; m; m &= m - 1)
+                            h ^= word[static_cast<size_t>(64) * w + __builtin_ctzll(m)];
+                    hash[(static_cast<size_t>(ch) << c->hash_shift) + p] = h;
+                }
+            }
+            if ((rc = put(&c->d_hash, hash.data(), hash.size() * sizeof(uint64_t)))) return rc;
+        }
     }
     if ((rc = put(&c->d_expected, c->expected.data(), c->expected.size()))) return rc;
     std::vector<uint8_t> kind(c->chan_kind.begin(), c->chan_kind.end());
@@ -1074,8 +1104,8 @@ static int screen_into(msc_ctx* ctx, const msc_circuit* c, int64_t n_shots,
     MSC_HIP(launch_prescreen(c->words, c->n_channels, n_shots, shot_off, chan, pauli,
                              static_cast<const uint64_t*>(c->d_sig),
                              static_cast<const int32_t*>(c->d_sig_off),
-                             static_cast<const uint8_t*>(c->d_kind), survive_bits, survivor_idx,
-                             tmp, nt, flag, ctx->stream));
+                             static_cast<const uint64_t*>(c->d_hash), c->hash_shift,
+                             survive_bits, survivor_idx, tmp, nt, flag, ctx->stream));
     MSC_HIP(hipEventRecord(ctx->ev1, ctx->stream));
     int64_t tail[2] = {0, 0};   // survivor total, flag word
     MSC_HIP(hipMemcpyAsync(tail, tmp + (nt - 2), sizeof(tail), hipMemcpyDeviceToHost,
@@ -1276,8 +1306,8 @@ extern "C" int msc_run_batch(msc_ctx* ctx, const msc_circuit* c, const msc_sim_o
         MSC_HIP(launch_prescreen(c->words, c->n_channels, n_shots, offp,
                                  static_cast<int32_t*>(dchan), static_cast<uint8_t*>(dpa),
                                  static_cast<const uint64_t*>(c->d_sig),
-                             static_cast<const int32_t*>(c->d_sig_off),
-                                 static_cast<const uint8_t*>(c->d_kind),
+                                 static_cast<const int32_t*>(c->d_sig_off),
+                                 static_cast<const uint64_t*>(c->d_hash), c->hash_shift,
                                  static_cast<uint64_t*>(dbits), idxp, static_cast<int64_t*>(dtp),
                                  ntp, csr_flag, ctx->stream));
     }

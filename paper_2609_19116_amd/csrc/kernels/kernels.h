@@ -162,11 +162,15 @@ enum CsrFlag : int {
 };
 // sig: per (channel, Pauli code) the fault's W-word signature; sig_off[c]
 // holds the index of channel c's first entry shifted left by two with the
-// channel's ChanKind in the low two bits (code_limit(kind) entries); kind:
-// ChanKind per channel (uint8); flag: one device int, cleared first
+// channel's ChanKind in the low two bits (code_limit(kind) entries); hash
+// (may be null): at (c << hash_shift) + code a 63-bit linear hash of that
+// signature, kHashInvalid for codes the channel does not have; flag: one
+// device int, cleared first
+constexpr uint64_t kHashInvalid = uint64_t(1) << 63;
+constexpr size_t kMaxHashEntries = size_t(1) << 23;    // 64 MiB
 hipError_t launch_prescreen(int words, int32_t n_channels, int64_t n, const int64_t* off, const int32_t* chan,
                             const uint8_t* pauli, const uint64_t* sig, const int32_t* sig_off,
-                            const uint8_t* kind,
+                            const uint64_t* hash, int hash_shift,
                             uint64_t* survive_bits, int64_t* survivor_idx, int64_t* block_tmp,
                             int64_t n_blocks_tmp, int* flag, hipStream_t s);
 int64_t prescreen_tmp_words(int64_t n);

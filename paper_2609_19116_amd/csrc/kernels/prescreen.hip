@@ -1,16 +1,15 @@
-// Offline-screening kernel (Section 4.2): one shot per lane.
+// Offline-screening kernel (Section 4.2).
 //
 // A shot's signature over the decided measurements is the XOR of its
 // faults' signatures; the shot must be simulated iff that signature is
 // zero.  A fault's signature (the XOR of its basis components, X and Z on
 // each of the channel's up to three qubits) is precombined per (channel,
-// Pauli code) on the host, so each fault costs one W-word lookup.  Each lane
-// streams its shot's CSR slice from HBM, XORs <= W-word signatures from the
-// L2-resident table in registers, and the wavefront's verdicts are packed
-// with a 64-lane ballot into one uint64 of the survivor bitmap (lane j of
-// wave w <-> shot 64 w + j).  A second pass turns the bitmap into an
-// ascending survivor index list: per-block popcounts, one scan block, and a
-// scatter with a per-wave prefix from the ballot mask.  Integer only.
+// Pauli code) on the host, so each fault costs one lookup in an L2-resident
+// table.  A block XORs its shots' lookups in LDS, and the wavefront's verdicts
+// are packed with a 64-lane ballot into one uint64 of the survivor bitmap (bit
+// j of word w <-> shot 64 w + j).  A second pass turns the bitmap into an
+// ascending survivor index list: popcounts per 256 shots, one scan block, and
+// a scatter with a per-wave prefix from the ballot mask.  Integer only.
 //
 // The CSR is checked on the way: a channel index outside [0, M), channels
 // not strictly ascending within a shot, a Pauli code that is zero or names
@@ -56,66 +55,240 @@ __device__ __forceinline__ int fault_check(int64_t c, int64_t prev, int p, int32
     return bad;
 }
 
+// One fault's checks and its signature XORed into acc (W words; CsrFlag bits
+// returned).  The channel's first table entry and its kind are one word.
+template <int W, typename F>
+__device__ __forceinline__ int screen_fault(int64_t c, int64_t prev, int p, int32_t nch,
+                                            const uint64_t* __restrict__ sig,
+                                            const int32_t* __restrict__ sig_off, F add) {
+    if (c < 0 || c >= nch) return CSR_BAD_CHANNEL;
+    const int32_t ek = sig_off[c];
+    int bad = c <= prev ? CSR_NOT_ASCENDING : 0;
+    // an invalid code has no entry (the call fails anyway)
+    if (p == 0 || p >= code_limit(ek & 3)) return bad | CSR_BAD_PAULI;
+    const uint64_t* s = sig + (static_cast<int64_t>(ek >> 2) + p) * W;
+#pragma unroll
+    for (int w = 0; w < W; ++w) add(w, s[w]);
+    return bad;
+}
+
+// One shot by its own lane, fault after fault: its checks (CsrFlag bits into
+// bad) and whether its signature is zero.
 template <int W>
-__global__ __launch_bounds__(PT) void screen_kernel(int32_t nch, int64_t n,
+__device__ bool screen_shot(int64_t f0, int64_t f1, int32_t nch, const int32_t* __restrict__ chan,
+                            const uint8_t* __restrict__ pauli, const uint64_t* __restrict__ sig,
+                            const int32_t* __restrict__ sig_off, int& bad) {
+    uint64_t acc[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) acc[w] = 0;
+    if (f1 < f0 || f0 < 0) bad |= CSR_BAD_OFFSETS;
+    int64_t prev = -1;
+    for (int64_t f = f0; f < f1; ++f) {
+        const int64_t c = chan[f];
+        bad |= screen_fault<W>(c, prev, pauli[f], nch, sig, sig_off,
+                               [&](int w, uint64_t x) { acc[w] ^= x; });
+        prev = c;
+    }
+    uint64_t any = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) any |= acc[w];
+    return any == 0;
+}
+
+// A block screens kShots shots, four per lane.  Its faults are one contiguous
+// run of the CSR when its offsets rise: they are dealt to the lanes one by one,
+// kScreenRun at a time (the screen is bound by the latency of offset, channel
+// and table reads one behind the other, so by how many a wavefront has in
+// flight).  A fault reads one word of the table, a linear hash of its
+// signature, XORed into its shot's word in LDS: a shot whose hashes do not XOR
+// to zero has a nonzero signature, which decides all but the survivors (and,
+// once in 2^63, another).  Those of them that have faults get a slot each, and
+// their faults, packed, XOR their W-word signatures into it (a walk by the
+// shot's lane where slots or the list run out).  A whole signature and its
+// entry's index are W + 1 gathers of 64 lines each.  2^24 shots of the
+// 81-qubit circuit: one lane per shot walking its faults 0.53 ms, faults dealt
+// to the lanes with whole signatures 0.54, with the hash 0.40, four shots per
+// lane and packed survivors 0.34 (0.41 with all kScreenPer table reads of a
+// lane in flight: 154 registers leave three wavefronts per SIMD).  Without a
+// hash (tables above kMaxHashEntries), and in blocks whose offsets fall or are
+// negative (the call fails), every shot is walked.
+constexpr int kSub = 4;                          // shots per lane
+constexpr int kShots = PT * kSub;
+constexpr int kScreenPer = 16, kScreenHash = 4;
+constexpr int kScreenRun = PT * kScreenPer;
+constexpr int kSlots = PT, kList = 2 * PT;
+template <int W>
+__global__ __launch_bounds__(PT, 4) void screen_kernel(int32_t nch, int64_t n,
                                                     const int64_t* __restrict__ off,
                                                     const int32_t* __restrict__ chan,
                                                     const uint8_t* __restrict__ pauli,
                                                     const uint64_t* __restrict__ sig,
                                                     const int32_t* __restrict__ sig_off,
-                                                    const uint8_t* __restrict__ /*kind*/,
+                                                    const uint64_t* __restrict__ hash, int shift,
                                                     uint64_t* __restrict__ bits,
                                                     int64_t* __restrict__ block_cnt,
                                                     int* __restrict__ flag) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * PT + threadIdx.x;
-    bool alive = false;
-    int bad = 0;
-    if (i < n) {
-        uint64_t acc[W];
+    __shared__ unsigned long long s_hash[kShots];
+    __shared__ int s_rel[kShots + 1];            // offsets from the block's first
+    __shared__ uint16_t s_own[kScreenRun];
+    __shared__ unsigned long long s_acc[W][kSlots];
+    __shared__ int16_t s_slot[kShots];           // -1: decided or walked
+    __shared__ int s_cnt[kSub][PT / 64], s_used, s_nf;
+    __shared__ int32_t s_lc[kList];
+    __shared__ uint16_t s_lp[kList];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kShots;
+    const int64_t first = off[i0];
+    bool alive[kSub];
+    int bad = 0, odd = !hash || first < 0;
+    int64_t e[kSub];
 #pragma unroll
-        for (int w = 0; w < W; ++w) acc[w] = 0;
-        const int64_t f0 = off[i], f1 = off[i + 1];
-        if (f1 < f0 || f0 < 0) bad |= CSR_BAD_OFFSETS;
-        int64_t prev = -1;
-        for (int64_t f = f0; f < f1; ++f) {
-            const int64_t c = chan[f];
-            const int p = pauli[f];
-            // the channel's first table entry and its kind, one load
-            const int32_t ek = c >= 0 && c < nch ? sig_off[c] : 0;
-            int fb = 0;
-            if (c < 0 || c >= nch) {
-                fb = CSR_BAD_CHANNEL;
-            } else {
-                fb = c <= prev ? CSR_NOT_ASCENDING : 0;
-                if (p == 0 || p >= code_limit(ek & 3)) fb |= CSR_BAD_PAULI;
-            }
-            bad |= fb;
-            prev = c;
-            // an invalid channel or code has no entry (the call fails anyway)
-            if (fb & (CSR_BAD_CHANNEL | CSR_BAD_PAULI)) continue;
-            const uint64_t* s = sig + (static_cast<int64_t>(ek >> 2) + p) * W;
-#pragma unroll
-            for (int w = 0; w < W; ++w) acc[w] ^= s[w];
-        }
-        uint64_t any = 0;
-#pragma unroll
-        for (int w = 0; w < W; ++w) any |= acc[w];
-        alive = any == 0;
+    for (int u = 0; u < kSub; ++u) {
+        const int64_t i = i0 + tid + PT * u;
+        e[u] = off[i + 1 < n ? i + 1 : n] - first;
     }
-    if (bad) atomicOr(flag, bad);
-    const uint64_t mask = __ballot(alive);
-    const int lane = threadIdx.x & 63;
-    const int64_t word = (static_cast<int64_t>(blockIdx.x) * PT + (threadIdx.x & ~63)) >> 6;
-    __shared__ int s_cnt[PT / 64];
-    if (lane == 0) {
-        if (word * 64 < n) bits[word] = mask;
-        s_cnt[threadIdx.x >> 6] = __popcll(mask);
+#pragma unroll
+    for (int u = 0; u < kSub; ++u) {
+        odd |= e[u] < 0 || e[u] >= (int64_t(1) << 31);
+        s_rel[tid + PT * u + 1] = static_cast<int>(e[u]);
+        s_hash[tid + PT * u] = 0;
+    }
+    if (tid == 0) {
+        s_rel[0] = 0;
+        s_used = 0;
+        s_nf = 0;
     }
     __syncthreads();
-    if (threadIdx.x == 0 && block_cnt) {
+#pragma unroll
+    for (int u = 0; u < kSub; ++u) odd |= s_rel[tid + PT * u + 1] < s_rel[tid + PT * u];
+    if (!__syncthreads_or(odd)) {
+        const int total = s_rel[kShots];
+        int32_t c[kScreenPer];
+        int p[kScreenPer];
+        for (int r0 = 0; r0 < total; r0 += kScreenRun) {
+            const int run = min(total - r0, kScreenRun);
+#pragma unroll
+            for (int u = 0; u < kScreenPer; ++u) {
+                const int f = tid + PT * u;
+                c[u] = -1;
+                p[u] = 0;
+                if (f < run) {
+                    c[u] = chan[first + r0 + f];
+                    p[u] = pauli[first + r0 + f];
+                }
+            }
+            // the shot of each fault of the run
+#pragma unroll
+            for (int u = 0; u < kSub; ++u) {
+                const int k = tid + PT * u;
+                const int lo = max(s_rel[k] - r0, 0), hi = min(s_rel[k + 1] - r0, run);
+                for (int f = lo; f < hi; ++f) s_own[f] = static_cast<uint16_t>(k);
+            }
+            __syncthreads();
+            // kScreenHash table reads in flight
+#pragma unroll
+            for (int u0 = 0; u0 < kScreenPer; u0 += kScreenHash) {
+                uint64_t h[kScreenHash];
+#pragma unroll
+                for (int v = 0; v < kScreenHash; ++v) {
+                    const int u = u0 + v;
+                    const bool in = c[u] >= 0 && c[u] < nch && !(p[u] >> shift);
+                    h[v] = hash[in ? (static_cast<int64_t>(c[u]) << shift) + p[u] : 0];
+                    if (!in) h[v] = kHashInvalid;
+                }
+#pragma unroll
+                for (int v = 0; v < kScreenHash; ++v) {
+                    const int u = u0 + v, f = tid + PT * u;
+                    // the channel before, from the lane below
+                    int32_t prev = __shfl_up(c[u], 1);
+                    if (f >= run) continue;
+                    if (lane == 0 && r0 + f > 0) prev = chan[first + r0 + f - 1];
+                    const int own = s_own[f];
+                    if (c[u] < 0 || c[u] >= nch) {
+                        bad |= CSR_BAD_CHANNEL;
+                        continue;
+                    }
+                    if (s_rel[own] < r0 + f && c[u] <= prev) bad |= CSR_NOT_ASCENDING;
+                    if (h[v] & kHashInvalid) bad |= CSR_BAD_PAULI;
+                    else if (h[v]) atomicXor(&s_hash[own], h[v]);
+                }
+            }
+            __syncthreads();
+        }
+        // slots for the shots left that have faults
+#pragma unroll
+        for (int u = 0; u < kSub; ++u) {
+            const int k = tid + PT * u;
+            alive[u] = i0 + k < n && s_hash[k] == 0;
+            int slot = -1;
+            if (total <= kScreenRun && alive[u] && s_rel[k + 1] > s_rel[k]) {
+                slot = atomicAdd(&s_used, 1);
+                if (slot >= kSlots) slot = -1;
+            }
+            s_slot[k] = static_cast<int16_t>(slot);
+        }
+#pragma unroll
+        for (int w = 0; w < W; ++w) s_acc[w][tid] = 0;
+        __syncthreads();
+        if (s_used) {
+            // their faults, packed: the lanes that read signatures are full
+#pragma unroll
+            for (int u = 0; u < kScreenPer; ++u) {
+                const int f = tid + PT * u;
+                const int slot = f < total ? s_slot[s_own[f]] : -1;
+                if (slot >= 0) {
+                    const int x = atomicAdd(&s_nf, 1);
+                    if (x < kList) {
+                        s_lc[x] = c[u];
+                        s_lp[x] = static_cast<uint16_t>(p[u] | (slot << 8));
+                    }
+                }
+            }
+            __syncthreads();
+            for (int x = tid; x < min(s_nf, kList); x += PT) {
+                const int slot = s_lp[x] >> 8;
+                (void)screen_fault<W>(s_lc[x], -1, s_lp[x] & 255, nch, sig, sig_off,   // (checked above)
+                                      [&](int w, uint64_t y) { atomicXor(&s_acc[w][slot], y); });
+            }
+            __syncthreads();
+        }
+        const bool listed = s_nf <= kList;
+#pragma unroll
+        for (int u = 0; u < kSub; ++u) {
+            const int k = tid + PT * u, slot = s_slot[k];
+            if (slot >= 0 && listed) {
+                uint64_t any = 0;
+#pragma unroll
+                for (int w = 0; w < W; ++w) any |= s_acc[w][slot];
+                alive[u] = any == 0;
+            } else if (alive[u] && s_rel[k + 1] > s_rel[k]) {
+                int again = 0;                   // (the checks are done)
+                alive[u] = screen_shot<W>(first + s_rel[k], first + s_rel[k + 1], nch, chan, pauli,
+                                          sig, sig_off, again);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < kSub; ++u) {
+            const int64_t i = i0 + tid + PT * u;
+            alive[u] = i < n && screen_shot<W>(off[i], off[i + 1], nch, chan, pauli, sig, sig_off, bad);
+        }
+    }
+    if (bad) atomicOr(flag, bad);
+#pragma unroll
+    for (int u = 0; u < kSub; ++u) {
+        const uint64_t mask = __ballot(alive[u]);
+        const int64_t word = (i0 + PT * u + (tid & ~63)) >> 6;
+        if (lane == 0) {
+            if (word * 64 < n) bits[word] = mask;
+            s_cnt[u][tid >> 6] = __popcll(mask);
+        }
+    }
+    __syncthreads();
+    if (tid < kSub && i0 + static_cast<int64_t>(PT) * tid < n && block_cnt) {
         int64_t t = 0;
-        for (int w = 0; w < PT / 64; ++w) t += s_cnt[w];
-        block_cnt[blockIdx.x] = t;
+        for (int w = 0; w < PT / 64; ++w) t += s_cnt[tid][w];
+        block_cnt[static_cast<int64_t>(blockIdx.x) * kSub + tid] = t;
     }
 }
 
@@ -220,9 +393,9 @@ int64_t prescreen_tmp_words(int64_t n) { return screen_tmp_words(n); }
 
 hipError_t launch_prescreen(int words, int32_t n_channels, int64_t n, const int64_t* off, const int32_t* chan,
                             const uint8_t* pauli, const uint64_t* sig, const int32_t* sig_off,
-                            const uint8_t* kind,
-                            uint64_t* bits, int64_t* survivor_idx, int64_t* block_tmp,
-                            int64_t n_blocks_tmp, int* flag, hipStream_t s) {
+                            const uint64_t* hash, int hash_shift, uint64_t* bits,
+                            int64_t* survivor_idx, int64_t* block_tmp, int64_t n_blocks_tmp,
+                            int* flag, hipStream_t s) {
     const int64_t nb = (n + PT - 1) / PT;
     if (nb == 0) return hipSuccess;
     const int64_t ns = (nb + kSup - 1) / kSup;
@@ -232,12 +405,12 @@ hipError_t launch_prescreen(int words, int32_t n_channels, int64_t n, const int6
     hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, s, flag);
     hipError_t e0 = hipGetLastError();
     if (e0 != hipSuccess) return e0;
-    dim3 grid(static_cast<unsigned>(nb));
+    dim3 grid(static_cast<unsigned>(nb)), sgrid(static_cast<unsigned>((nb + kSub - 1) / kSub));
     switch (words) {
 #define MSC_SCREEN_CASE(WW)                                                                   \
     case WW:                                                                                  \
-        hipLaunchKernelGGL(screen_kernel<WW>, grid, dim3(PT), 0, s, n_channels, n, off, chan,  \
-                           pauli, sig, sig_off, kind, bits, block_tmp, flag);                 \
+        hipLaunchKernelGGL(screen_kernel<WW>, sgrid, dim3(PT), 0, s, n_channels, n, off, chan, \
+                           pauli, sig, sig_off, hash, hash_shift, bits, block_tmp, flag);     \
         break;
         MSC_SCREEN_CASE(1)
         MSC_SCREEN_CASE(2)
