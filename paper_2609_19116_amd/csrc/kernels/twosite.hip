@@ -9,7 +9,11 @@
 // through double-buffered LDS in steps of 16.  Each wave keeps a 64 x (32 b,
 // both j') accumulator block, so the four (i', j') partial products of an
 // output (a, b) sit in the same lane and the 4x4 gate is applied in
-// registers before the single store of theta.
+// registers before the single store of theta.  Bound by the FP32 matrix rate
+// (153 TFLOP/s in a large product): two workgroups per CU, so that one's
+// products run while the other waits at a barrier or stores theta; chi 256,
+// batch 192: 0.82 ms, 128 TFLOP/s (one workgroup, A transposed into LDS by
+// 4-byte stores: 1.08 ms, 97).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -34,13 +38,20 @@ __device__ __forceinline__ int xcd_block(int h, int nb) {
     return (nb & 7) ? h : (h & 7) * (nb >> 3) + (h >> 3);
 }
 
-__global__ __launch_bounds__(NTH) void twosite_kernel(int chi, int tiles, const float* __restrict__ Ag,
+constexpr int AP = TK + 4;       // padded row of A in LDS
+constexpr int BP = 2 * TB + 4;   // padded row of B in LDS
+
+// MFMA step ks of a stage takes k = 4 g + ks from lane group g, of A and of B
+// alike (the products of a sum may be taken in any order), so a lane's A
+// operands of four steps are 16 bytes of one row: A goes to LDS as it lies in
+// memory, and both paddings spread the four groups over the banks.
+__global__ __launch_bounds__(NTH, 2) void twosite_kernel(int chi, int tiles, const float* __restrict__ Ag,
                                                       const float* __restrict__ Bg,
                                                       const float* __restrict__ gate,
                                                       float* __restrict__ Tg) {
-    // LDS: [stage][plane][k][col]
-    __shared__ float As[2][2][TK][TM];
-    __shared__ float Bs[2][2][TK][2 * TB];
+    // LDS: [stage][plane][row][k] and [stage][plane][k][col]
+    __shared__ __attribute__((aligned(16))) float As[2][2][TM][AP];
+    __shared__ __attribute__((aligned(16))) float Bs[2][2][TK][BP];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -72,19 +83,19 @@ __global__ __launch_bounds__(NTH) void twosite_kernel(int chi, int tiles, const 
 #pragma unroll
                 for (int d = 0; d < 2; ++d) acc[a][b][c][d] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    float4 ra[4], rb[4];
+    floatx4 ra[4], rb[4];
     auto gload = [&](int k0) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const int idx = tid + NTH * s;
             const int plane = idx >> 9, rem = idx & 511;
             const int row = rem >> 2, kq = rem & 3;
-            ra[s] = *reinterpret_cast<const float4*>(A + (size_t)plane * m * chi +
+            ra[s] = *reinterpret_cast<const floatx4*>(A + (size_t)plane * m * chi +
                                                      (size_t)(R0 + row) * chi + k0 + 4 * kq);
             const int kr = rem >> 5, cq = rem & 31;
             const int cl = 4 * cq;
             const int col = (cl >> 6) * chi + B0 + (cl & 63);
-            rb[s] = *reinterpret_cast<const float4*>(Bm + (size_t)plane * chi * n +
+            rb[s] = *reinterpret_cast<const floatx4*>(Bm + (size_t)plane * chi * n +
                                                      (size_t)(k0 + kr) * n + col);
         }
     };
@@ -94,12 +105,9 @@ __global__ __launch_bounds__(NTH) void twosite_kernel(int chi, int tiles, const 
             const int idx = tid + NTH * s;
             const int plane = idx >> 9, rem = idx & 511;
             const int row = rem >> 2, kq = rem & 3;
-            As[st][plane][4 * kq + 0][row] = ra[s].x;
-            As[st][plane][4 * kq + 1][row] = ra[s].y;
-            As[st][plane][4 * kq + 2][row] = ra[s].z;
-            As[st][plane][4 * kq + 3][row] = ra[s].w;
+            *reinterpret_cast<floatx4*>(&As[st][plane][row][4 * kq]) = ra[s];
             const int kr = rem >> 5, cq = rem & 31;
-            *reinterpret_cast<float4*>(&Bs[st][plane][kr][4 * cq]) = rb[s];
+            *reinterpret_cast<floatx4*>(&Bs[st][plane][kr][4 * cq]) = rb[s];
         }
     };
 
@@ -110,23 +118,24 @@ __global__ __launch_bounds__(NTH) void twosite_kernel(int chi, int tiles, const 
     for (int kt = 0; kt < nk; ++kt) {
         const int st = kt & 1;
         if (kt + 1 < nk) gload((kt + 1) * TK);
+        const int grp = lane >> 4;
+        floatx4 ar[4], ai[4];
 #pragma unroll
-        for (int ks = 0; ks < TK / 4; ++ks) {
-            const int kk = 4 * ks + (lane >> 4);
-            float ar[4], ai[4], br[2][2], bi[2][2];
+        for (int mt = 0; mt < 4; ++mt) {
+            const int r = wm * 64 + mt * 16 + (lane & 15);
+            ar[mt] = *reinterpret_cast<const floatx4*>(&As[st][0][r][4 * grp]);
+            ai[mt] = *reinterpret_cast<const floatx4*>(&As[st][1][r][4 * grp]);
+        }
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                const int r = wm * 64 + mt * 16 + (lane & 15);
-                ar[mt] = As[st][0][kk][r];
-                ai[mt] = As[st][1][kk][r];
-            }
+        for (int ks = 0; ks < 4; ++ks) {
+            float br[2][2], bi[2][2];
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
                 for (int jp = 0; jp < 2; ++jp) {
                     const int c = jp * TB + wn * 32 + nt * 16 + (lane & 15);
-                    br[nt][jp] = Bs[st][0][kk][c];
-                    bi[nt][jp] = Bs[st][1][kk][c];
+                    br[nt][jp] = Bs[st][0][4 * grp + ks][c];
+                    bi[nt][jp] = Bs[st][1][4 * grp + ks][c];
                 }
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt)
@@ -136,10 +145,10 @@ __global__ __launch_bounds__(NTH) void twosite_kernel(int chi, int tiles, const 
                     for (int jp = 0; jp < 2; ++jp) {
                         floatx4& re = acc[mt][nt][jp][0];
                         floatx4& im = acc[mt][nt][jp][1];
-                        re = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[mt], br[nt][jp], re, 0, 0, 0);
-                        re = __builtin_amdgcn_mfma_f32_16x16x4f32(-ai[mt], bi[nt][jp], re, 0, 0, 0);
-                        im = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[mt], bi[nt][jp], im, 0, 0, 0);
-                        im = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[mt], br[nt][jp], im, 0, 0, 0);
+                        re = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[mt][ks], br[nt][jp], re, 0, 0, 0);
+                        im = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[mt][ks], bi[nt][jp], im, 0, 0, 0);
+                        re = __builtin_amdgcn_mfma_f32_16x16x4f32(-ai[mt][ks], bi[nt][jp], re, 0, 0, 0);
+                        im = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[mt][ks], br[nt][jp], im, 0, 0, 0);
                     }
         }
         if (kt + 1 < nk) lstore(st ^ 1);
