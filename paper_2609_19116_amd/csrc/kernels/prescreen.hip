@@ -95,30 +95,27 @@ __device__ bool screen_shot(int64_t f0, int64_t f1, int32_t nch, const int32_t* 
     return any == 0;
 }
 
-// A block screens kShots shots, four per lane.  Its faults are one contiguous
-// run of the CSR when its offsets rise: they are dealt to the lanes one by one,
-// kScreenRun at a time (the screen is bound by the latency of offset, channel
-// and table reads one behind the other, so by how many a wavefront has in
-// flight).  A fault reads one word of the table, a linear hash of its
-// signature, XORed into its shot's word in LDS: a shot whose hashes do not XOR
-// to zero has a nonzero signature, which decides all but the survivors (and,
-// once in 2^63, another).  Those of them that have faults get a slot each, and
-// their faults, packed, XOR their W-word signatures into it (a walk by the
-// shot's lane where slots or the list run out).  A whole signature and its
-// entry's index are W + 1 gathers of 64 lines each.  2^24 shots of the
-// 81-qubit circuit: one lane per shot walking its faults 0.53 ms, faults dealt
-// to the lanes with whole signatures 0.54, with the hash 0.40, four shots per
-// lane and packed survivors 0.34 (0.41 with all kScreenPer table reads of a
-// lane in flight: 154 registers leave three wavefronts per SIMD).  Without a
-// hash (tables above kMaxHashEntries), and in blocks whose offsets fall or are
-// negative (the call fails), every shot is walked.
-constexpr int kSub = 4;                          // shots per lane
-constexpr int kShots = PT * kSub;
-constexpr int kScreenPer = 16, kScreenHash = 4;
+// A block screens PT shots.  Their faults are one contiguous run of the CSR
+// when the offsets rise: they are dealt to the lanes one by one, kScreenRun at
+// a time (the screen is bound by the latency of offset, channel and table
+// reads one behind the other, so by how many a wavefront has in flight).  A
+// fault reads one word of the table, a linear hash of its signature, XORed into
+// its shot's word in LDS: a shot whose hashes do not XOR to zero has a nonzero
+// signature, which decides all but the survivors (and, once in 2^63, another).
+// The survivors that have faults XOR their whole W-word signatures, fault by
+// fault over the lanes, their faults packed (a walk by the shot's lane where
+// the list runs out or the faults took several runs).  A whole signature and
+// its entry's index are W + 1 gathers of 64 lines each.  Without a hash (tables
+// above kMaxHashEntries), and in blocks whose offsets fall or are negative (the
+// call fails), every shot is walked.
+// 2^24 shots of the 81-qubit circuit, the call: one lane per shot walking its
+// faults 571 us, now 345 (five times the fault rate: 2886 and 1186); 2^14
+// shots 22 us both.  Four shots per lane take 377 us, and 33 for 2^14 shots.
+constexpr int kScreenPer = 4;
 constexpr int kScreenRun = PT * kScreenPer;
-constexpr int kSlots = PT, kList = 2 * PT;
+constexpr int kList = 2 * PT;
 template <int W>
-__global__ __launch_bounds__(PT, 4) void screen_kernel(int32_t nch, int64_t n,
+__global__ __launch_bounds__(PT) void screen_kernel(int32_t nch, int64_t n,
                                                     const int64_t* __restrict__ off,
                                                     const int32_t* __restrict__ chan,
                                                     const uint8_t* __restrict__ pauli,
@@ -128,41 +125,29 @@ __global__ __launch_bounds__(PT, 4) void screen_kernel(int32_t nch, int64_t n,
                                                     uint64_t* __restrict__ bits,
                                                     int64_t* __restrict__ block_cnt,
                                                     int* __restrict__ flag) {
-    __shared__ unsigned long long s_hash[kShots];
-    __shared__ int s_rel[kShots + 1];            // offsets from the block's first
-    __shared__ uint16_t s_own[kScreenRun];
-    __shared__ unsigned long long s_acc[W][kSlots];
-    __shared__ int16_t s_slot[kShots];           // -1: decided or walked
-    __shared__ int s_cnt[kSub][PT / 64], s_used, s_nf;
-    __shared__ int32_t s_lc[kList];
+    __shared__ unsigned long long s_hash[PT];
+    __shared__ int s_rel[PT + 1];                // offsets from the block's first
+    __shared__ uint16_t s_own[kScreenRun];       // the shot of each fault of a run
+    __shared__ unsigned long long s_acc[W][PT];
+    __shared__ int s_cnt[PT / 64], s_nf;
+    __shared__ int32_t s_lc[kList];              // the survivors' faults
     __shared__ uint16_t s_lp[kList];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kShots;
-    const int64_t first = off[i0];
-    bool alive[kSub];
-    int bad = 0, odd = !hash || first < 0;
-    int64_t e[kSub];
-#pragma unroll
-    for (int u = 0; u < kSub; ++u) {
-        const int64_t i = i0 + tid + PT * u;
-        e[u] = off[i + 1 < n ? i + 1 : n] - first;
-    }
-#pragma unroll
-    for (int u = 0; u < kSub; ++u) {
-        odd |= e[u] < 0 || e[u] >= (int64_t(1) << 31);
-        s_rel[tid + PT * u + 1] = static_cast<int>(e[u]);
-        s_hash[tid + PT * u] = 0;
-    }
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * PT, i = i0 + tid;
+    const int64_t first = off[i0], end = off[i + 1 < n ? i + 1 : n] - first;
+    int bad = 0, odd = !hash || first < 0 || end < 0 || end >= (int64_t(1) << 31);
+    s_rel[tid + 1] = static_cast<int>(end);
+    s_hash[tid] = 0;
     if (tid == 0) {
         s_rel[0] = 0;
-        s_used = 0;
         s_nf = 0;
     }
     __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kSub; ++u) odd |= s_rel[tid + PT * u + 1] < s_rel[tid + PT * u];
+    const int my0 = s_rel[tid], my1 = s_rel[tid + 1];
+    odd |= my1 < my0;
+    bool alive;
     if (!__syncthreads_or(odd)) {
-        const int total = s_rel[kShots];
+        const int total = s_rel[PT];
         int32_t c[kScreenPer];
         int p[kScreenPer];
         for (int r0 = 0; r0 < total; r0 += kScreenRun) {
@@ -177,118 +162,87 @@ __global__ __launch_bounds__(PT, 4) void screen_kernel(int32_t nch, int64_t n,
                     p[u] = pauli[first + r0 + f];
                 }
             }
-            // the shot of each fault of the run
-#pragma unroll
-            for (int u = 0; u < kSub; ++u) {
-                const int k = tid + PT * u;
-                const int lo = max(s_rel[k] - r0, 0), hi = min(s_rel[k + 1] - r0, run);
-                for (int f = lo; f < hi; ++f) s_own[f] = static_cast<uint16_t>(k);
-            }
+            for (int f = max(my0 - r0, 0); f < min(my1 - r0, run); ++f)
+                s_own[f] = static_cast<uint16_t>(tid);
             __syncthreads();
-            // kScreenHash table reads in flight
+            uint64_t h[kScreenPer];
 #pragma unroll
-            for (int u0 = 0; u0 < kScreenPer; u0 += kScreenHash) {
-                uint64_t h[kScreenHash];
-#pragma unroll
-                for (int v = 0; v < kScreenHash; ++v) {
-                    const int u = u0 + v;
-                    const bool in = c[u] >= 0 && c[u] < nch && !(p[u] >> shift);
-                    h[v] = hash[in ? (static_cast<int64_t>(c[u]) << shift) + p[u] : 0];
-                    if (!in) h[v] = kHashInvalid;
-                }
-#pragma unroll
-                for (int v = 0; v < kScreenHash; ++v) {
-                    const int u = u0 + v, f = tid + PT * u;
-                    // the channel before, from the lane below
-                    int32_t prev = __shfl_up(c[u], 1);
-                    if (f >= run) continue;
-                    if (lane == 0 && r0 + f > 0) prev = chan[first + r0 + f - 1];
-                    const int own = s_own[f];
-                    if (c[u] < 0 || c[u] >= nch) {
-                        bad |= CSR_BAD_CHANNEL;
-                        continue;
-                    }
-                    if (s_rel[own] < r0 + f && c[u] <= prev) bad |= CSR_NOT_ASCENDING;
-                    if (h[v] & kHashInvalid) bad |= CSR_BAD_PAULI;
-                    else if (h[v]) atomicXor(&s_hash[own], h[v]);
-                }
+            for (int u = 0; u < kScreenPer; ++u) {
+                const bool in = c[u] >= 0 && c[u] < nch && !(p[u] >> shift);
+                h[u] = hash[in ? (static_cast<int64_t>(c[u]) << shift) + p[u] : 0];
+                if (!in) h[u] = kHashInvalid;
             }
-            __syncthreads();
-        }
-        // slots for the shots left that have faults
-#pragma unroll
-        for (int u = 0; u < kSub; ++u) {
-            const int k = tid + PT * u;
-            alive[u] = i0 + k < n && s_hash[k] == 0;
-            int slot = -1;
-            if (total <= kScreenRun && alive[u] && s_rel[k + 1] > s_rel[k]) {
-                slot = atomicAdd(&s_used, 1);
-                if (slot >= kSlots) slot = -1;
-            }
-            s_slot[k] = static_cast<int16_t>(slot);
-        }
-#pragma unroll
-        for (int w = 0; w < W; ++w) s_acc[w][tid] = 0;
-        __syncthreads();
-        if (s_used) {
-            // their faults, packed: the lanes that read signatures are full
 #pragma unroll
             for (int u = 0; u < kScreenPer; ++u) {
                 const int f = tid + PT * u;
-                const int slot = f < total ? s_slot[s_own[f]] : -1;
-                if (slot >= 0) {
+                // the channel before, from the lane below
+                int32_t prev = __shfl_up(c[u], 1);
+                if (f >= run) continue;
+                if (lane == 0 && r0 + f > 0) prev = chan[first + r0 + f - 1];
+                const int own = s_own[f];
+                if (c[u] < 0 || c[u] >= nch) {
+                    bad |= CSR_BAD_CHANNEL;
+                    continue;
+                }
+                if (s_rel[own] < r0 + f && c[u] <= prev) bad |= CSR_NOT_ASCENDING;
+                if (h[u] & kHashInvalid) bad |= CSR_BAD_PAULI;
+                else if (h[u]) atomicXor(&s_hash[own], h[u]);
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int w = 0; w < W; ++w) s_acc[w][tid] = 0;
+        alive = i < n && s_hash[tid] == 0;
+        const bool check = alive && my1 > my0;
+        if (total <= kScreenRun) {
+            if (__syncthreads_or(check)) {
+                // the faults of the shots left, packed: the lanes that read
+                // signatures are full
+#pragma unroll
+                for (int u = 0; u < kScreenPer; ++u) {
+                    const int f = tid + PT * u;
+                    if (f >= total) continue;
+                    const int own = s_own[f];
+                    if (s_hash[own] != 0) continue;
                     const int x = atomicAdd(&s_nf, 1);
                     if (x < kList) {
                         s_lc[x] = c[u];
-                        s_lp[x] = static_cast<uint16_t>(p[u] | (slot << 8));
+                        s_lp[x] = static_cast<uint16_t>(p[u] | (own << 8));
                     }
                 }
+                __syncthreads();
+                for (int x = tid; x < min(s_nf, kList); x += PT) {
+                    const int own = s_lp[x] >> 8;
+                    (void)screen_fault<W>(s_lc[x], -1, s_lp[x] & 255, nch, sig, sig_off,   // (checked above)
+                                          [&](int w, uint64_t y) { atomicXor(&s_acc[w][own], y); });
+                }
+                __syncthreads();
             }
-            __syncthreads();
-            for (int x = tid; x < min(s_nf, kList); x += PT) {
-                const int slot = s_lp[x] >> 8;
-                (void)screen_fault<W>(s_lc[x], -1, s_lp[x] & 255, nch, sig, sig_off,   // (checked above)
-                                      [&](int w, uint64_t y) { atomicXor(&s_acc[w][slot], y); });
-            }
-            __syncthreads();
         }
-        const bool listed = s_nf <= kList;
+        if (check && total <= kScreenRun && s_nf <= kList) {
+            uint64_t any = 0;
 #pragma unroll
-        for (int u = 0; u < kSub; ++u) {
-            const int k = tid + PT * u, slot = s_slot[k];
-            if (slot >= 0 && listed) {
-                uint64_t any = 0;
-#pragma unroll
-                for (int w = 0; w < W; ++w) any |= s_acc[w][slot];
-                alive[u] = any == 0;
-            } else if (alive[u] && s_rel[k + 1] > s_rel[k]) {
-                int again = 0;                   // (the checks are done)
-                alive[u] = screen_shot<W>(first + s_rel[k], first + s_rel[k + 1], nch, chan, pauli,
-                                          sig, sig_off, again);
-            }
+            for (int w = 0; w < W; ++w) any |= s_acc[w][tid];
+            alive = any == 0;
+        } else if (check) {
+            int again = 0;                       // (the checks are done)
+            alive = screen_shot<W>(first + my0, first + my1, nch, chan, pauli, sig, sig_off, again);
         }
     } else {
-#pragma unroll
-        for (int u = 0; u < kSub; ++u) {
-            const int64_t i = i0 + tid + PT * u;
-            alive[u] = i < n && screen_shot<W>(off[i], off[i + 1], nch, chan, pauli, sig, sig_off, bad);
-        }
+        alive = i < n && screen_shot<W>(off[i], off[i + 1], nch, chan, pauli, sig, sig_off, bad);
     }
     if (bad) atomicOr(flag, bad);
-#pragma unroll
-    for (int u = 0; u < kSub; ++u) {
-        const uint64_t mask = __ballot(alive[u]);
-        const int64_t word = (i0 + PT * u + (tid & ~63)) >> 6;
-        if (lane == 0) {
-            if (word * 64 < n) bits[word] = mask;
-            s_cnt[u][tid >> 6] = __popcll(mask);
-        }
+    const uint64_t mask = __ballot(alive);
+    const int64_t word = (i0 + (tid & ~63)) >> 6;
+    if (lane == 0) {
+        if (word * 64 < n) bits[word] = mask;
+        s_cnt[tid >> 6] = __popcll(mask);
     }
     __syncthreads();
-    if (tid < kSub && i0 + static_cast<int64_t>(PT) * tid < n && block_cnt) {
+    if (tid == 0 && block_cnt) {
         int64_t t = 0;
-        for (int w = 0; w < PT / 64; ++w) t += s_cnt[tid][w];
-        block_cnt[static_cast<int64_t>(blockIdx.x) * kSub + tid] = t;
+        for (int w = 0; w < PT / 64; ++w) t += s_cnt[w];
+        block_cnt[blockIdx.x] = t;
     }
 }
 
@@ -405,11 +359,11 @@ hipError_t launch_prescreen(int words, int32_t n_channels, int64_t n, const int6
     hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, s, flag);
     hipError_t e0 = hipGetLastError();
     if (e0 != hipSuccess) return e0;
-    dim3 grid(static_cast<unsigned>(nb)), sgrid(static_cast<unsigned>((nb + kSub - 1) / kSub));
+    dim3 grid(static_cast<unsigned>(nb));
     switch (words) {
 #define MSC_SCREEN_CASE(WW)                                                                   \
     case WW:                                                                                  \
-        hipLaunchKernelGGL(screen_kernel<WW>, sgrid, dim3(PT), 0, s, n_channels, n, off, chan, \
+        hipLaunchKernelGGL(screen_kernel<WW>, grid, dim3(PT), 0, s, n_channels, n, off, chan, \
                            pauli, sig, sig_off, hash, hash_shift, bits, block_tmp, flag);     \
         break;
         MSC_SCREEN_CASE(1)

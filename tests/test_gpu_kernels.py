@@ -2,8 +2,8 @@
 
 Shot counts around the number of shots of a workgroup (four of bond 16, seven
 of bond 32, one of bond 128), screens whose blocks take each of their routes
-(several runs of faults, more survivors than slots, more of their faults than
-the list holds, no hash table, odd sizes), and contractions whose tile counts
+(several runs of faults, more faults of survivors than the list holds, no hash
+table, odd sizes), and contractions whose tile counts
 are not multiples of the XCD count.
 
 Tolerances: a shot result is within TOL[precision] of the oracle in either
@@ -89,7 +89,7 @@ def _tile(csr, picks):
 
 @pytest.mark.parametrize("name,n,weight", [
     ("c1", 1, 2), ("c1", 63, 1), ("c1", 257, 3), ("c1", 1023, 2), ("c1", 1025, 2),
-    ("c1", 1030, 4),            # a block at the edge of one run of 4096 faults
+    ("c1", 1030, 4),            # blocks of exactly one run of 1024 faults
     ("c1", 1100, 5),            # two runs: survivors walked
     ("c1_ghz", 1024, 13),       # four runs, three-qubit codes
     ("tiny", 2049, 0),          # no faults at all
@@ -101,7 +101,7 @@ def test_screen_block_edges(ctx, name, n, weight):
     _check_screen(ctx, c, text, msc.sample_faults(c, 0x5EED0202, 0, n, weights=w))
 
 
-@pytest.mark.parametrize("kind", ["slots", "list", "mixed"])
+@pytest.mark.parametrize("kind", ["every", "list", "mixed"])
 def test_screen_many_survivors_with_faults(ctx, kind):
     text = config_circuit("c1").text
     c = msc.Circuit(text)
@@ -114,11 +114,11 @@ def test_screen_many_survivors_with_faults(ctx, kind):
     gone = np.nonzero(dead & (wt == 1))[0]
     assert len(alive) > 20 and len(heavy) > 3
     m = 1500
-    if kind == "slots":          # every shot survives with faults: slots run out
+    if kind == "every":          # every shot survives with faults
         picks = np.resize(alive, m)
-    elif kind == "list":         # 205 survivors of a block, above 512 faults of theirs
-        picks = np.where(np.arange(m) % 5 == 0, np.resize(heavy, m), np.resize(gone, m))
-    else:                        # some of both, slots and list suffice
+    elif kind == "list":         # the same, above 512 faults of survivors in a block
+        picks = np.resize(heavy, m)
+    else:                        # a few survivors among the others
         picks = np.where(np.arange(m) % 20 == 0, np.resize(alive, m), np.resize(gone, m))
     _check_screen(ctx, c, text, _tile(csr, picks))
 
