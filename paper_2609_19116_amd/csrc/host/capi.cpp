@@ -869,7 +869,8 @@ static int ensure_prefix(msc_ctx* ctx, msc_circuit* c, const RunCfg& cfg) {
     const double tau = cfg.tau, tau_rej = cfg.tau_rej;
     if (pk.valid && pk.dev == ctx->device && pk.precision == precision &&
         pk.chi_max == chi_max && pk.lds_width == lds_width && pk.tau == tau &&
-        pk.tau_rej == tau_rej && pk.park_side == cfg.park_side && pk.wave_chi == cfg.wave_chi)
+        pk.tau_rej == tau_rej && pk.park_side == cfg.park_side && pk.wave_chi == cfg.wave_chi &&
+        pk.fast_wide == cfg.fast_wide)
         return MSC_OK;
     free_prefix(pk);
     pk.dev = ctx->device;
@@ -933,6 +934,7 @@ static int ensure_prefix(msc_ctx* ctx, msc_circuit* c, const RunCfg& cfg) {
     pk.lds_width = lds_width;
     pk.park_side = cfg.park_side;
     pk.wave_chi = cfg.wave_chi;
+    pk.fast_wide = cfg.fast_wide;
     pk.tau = tau;
     pk.tau_rej = tau_rej;
     pk.build_ms = static_cast<float>(ctx->last_ms["prefix"]);

@@ -83,6 +83,7 @@ int set_error(int code, const std::string& msg);
 struct PrefixCk {
     bool valid = false;
     int dev = -1, precision = -1, chi_max = 0, lds_width = 0, park_side = 0, wave_chi = 0;
+    bool fast_wide = false;
     double tau = 0.0, tau_rej = 0.0;
     int n_ck = 0, ck_k = 1, avail = 0;
     int64_t cap = 0;           // elements of the tensor type

@@ -66,6 +66,25 @@ def test_matrix_core_shots_match_workgroup_kernel(ctx, name, sizes, precision):
         assert np.all(np.abs(got["infid"] - r["infid"])[acc] <= 2 * TOL[precision] * scale)
 
 
+def test_checkpoints_belong_to_the_kernel_that_recorded_them(ctx):
+    # bond 32: an explicit wave_chi 32 runs the general wavefront kernel, the
+    # automatic choice the matrix-core kernel of the same cap; a forked run
+    # repeats its own kernel's bits whichever recorded checkpoints before
+    c = msc.Circuit(config_circuit("c3").text)
+    say("calibrate c3")
+    c.calibrate(ctx)
+    n = 24
+    off, ch, pa = to_dev(*msc.sample_faults(c, 0x5EED0207, 0, n,
+                                            weights=(np.arange(n) % 3).astype(np.int32)))
+    kw = dict(precision=MSC_FP32)
+    for chi in (0, 32, 0):
+        say(f"forked and plain wave_chi={chi}")
+        a = results_numpy(msc.simulate(ctx, c, off, ch, pa, wave_chi=chi, **kw))
+        b = results_numpy(msc.simulate(ctx, c, off, ch, pa, wave_chi=chi, prefix=True, **kw))
+        for f in ("p_acc", "infid", "chi_peak", "status", "rejected_at", "fail"):
+            assert np.array_equal(a[f], b[f]), (chi, f)
+
+
 def _check_screen(ctx, c, text, csr):
     from oracle.ir import parse
     n = len(csr[0]) - 1
