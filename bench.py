@@ -3,8 +3,8 @@
 A step is one pass of the hot path over one batch of shots, one library
 call on one HIP stream: subset-sampled faults drawn on the GPU from the
 seed (Section 4.1), the bit-exact offline screen over the batch, batched
-mixed-precision MPS simulation (FP32 contractions, FP64 SVD, norms and
-probabilities) of the survivors in one persistent launch, and the
+mixed-precision MPS simulation (FP32 tensors, FP64 contractions, SVD, norms
+and probabilities) of the survivors in one persistent launch, and the
 per-weight bin sums that feed Eq. (reweight).  Workload: the 49-qubit
 rotated d=5 circuit (6 noisy rounds, two transversal T layers), p = 1e-3,
 chi_max = 256, 2^19 shots per step (128 batches of the workload's 4096
@@ -285,13 +285,11 @@ def main() -> int:
     # With one step in flight the launches do not overlap, so this is the
     # rate the kernel trace of the same command gives per launch.
     achieved = float(np.mean(flops)) / (float(np.mean(sim_ms)) * 1e-3) / 1e12
-    # which shot kernel ran the steps: the wavefront kernel (one shot per
-    # wavefront) or the workgroup kernel
+    # which shot kernel ran the steps (the instance without checkpoint
+    # recording and segment reach, which the timed steps do not use)
     wave_slots = ctxs[0].engine_stats()["wave_slots"]
-    # (the wavefront kernel's instance without checkpoint recording and
-    # segment reach, which the timed steps do not use)
-    kernel_name = ("mps_wave_kernel<float, false>" if wave_slots else
-                   f"mps_kernel<float,{64 if args.lds_width == 64 else 32}>")
+    kernel_name = shot_kernel(wave_slots, args.wave_chi, args.lds_width,
+                              circ.noiseless()["chi_peak"])
     achieved_job = sum(flops) / wall / 1e12
     sweeps = sum(st["sweeps"] for st in sts)
     log(f"steps={args.steps} wall={wall:.3f}s value={value:.1f} shots/s survivors={n_surv} "
@@ -320,8 +318,8 @@ def main() -> int:
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "f32",
-        "precision": "FP32 split-complex contractions and tensors; FP64 one-sided Jacobi SVD, "
-                     "renormalisation, measurement probabilities and P_acc",
+        "precision": "FP32 split-complex tensors; contractions, factorisations, "
+                     "renormalisation, measurement probabilities and P_acc in FP64",
         "data": "synthetic: seeded cultivation-like circuit and seeded subset-sampled faults",
         "config": {"workload": "rotated d=5 cultivation-like circuit, 49 qubits (25 data + 24 "
                                "ancilla), 6 noisy rounds, two T layers; p=1e-3 depolarising; "
@@ -358,9 +356,9 @@ def main() -> int:
                      "frac_whole_job": achieved_job / PEAK_VALU,
                      "frac_of_fp32_packed_peak": achieved / PEAK_FP32,
                      "note": "vector-ALU peak without packed FP32 FMAs (256 CUs x 64 lanes x "
-                             "2 flops x 2.4 GHz = 78.6 TFLOP/s, FP32 and FP64 alike): the "
-                             "contraction is FP32, the Jacobi SVD, norms and projection FP64; "
-                             "the kernel is built without packed FP32 instructions"},
+                             "2 flops x 2.4 GHz = 78.6 TFLOP/s, FP32 and FP64 alike), also the "
+                             "FP64 matrix peak: contractions, Gram matrices and projections "
+                             "run on FP64 MFMA"},
         "estimates": {str(p): e for p, e in zip([5e-4, 1e-3, 2e-3], est)},
         "intervals_r100": intervals,
         "order_search": order_info,
@@ -617,11 +615,23 @@ def workloads_17q(msc, ctx) -> dict:
             line[pname] = {"ms": t, "shots_per_s": n17 / (t * 1e-3),
                            "gate_updates_per_s": float(r17["n2q"].sum()) / (t * 1e-3),
                            "chi_peak": int(r17["chi_peak"].max()),
-                           "kernel": ("mps_wave_kernel" if ctx.engine_stats()["wave_slots"]
-                                      else "mps_kernel")}
+                           "kernel": shot_kernel(ctx.engine_stats()["wave_slots"], 0, 0,
+                                                 c17.noiseless()["chi_peak"]).split("<")[0]}
         lines[name] = line
         del o17, ch17, pa17
     return lines
+
+
+def shot_kernel(wave_slots: int, wave_chi: int, lds_width: int, chi_peak: int) -> str:
+    """The shot kernel that FP32 runs of a circuit without CS and CCZ take
+    (chi_peak: bond of its noiseless run): one shot per wavefront up to bond
+    16 (wave_slots > 0) and 32, one per workgroup on the matrix cores up to
+    128, the general workgroup kernel otherwise."""
+    if wave_slots:
+        return f"mps_{'fast_' if wave_chi <= 16 else ''}wave_kernel<float, false>"
+    if wave_chi == 0 and lds_width == 0 and chi_peak <= 128:
+        return f"mps_fast_{'mid' if chi_peak <= 32 else 'group'}_kernel<float, false>"
+    return f"mps_kernel<float,{64 if lds_width == 64 else 32}>"
 
 
 def measured_traffic(layout_key: str, kernel_name: str):
@@ -629,8 +639,9 @@ def measured_traffic(layout_key: str, kernel_name: str):
     that kernel, or None when the kernel source or the layout changed since
     the counters were taken."""
     import hashlib
-    src = os.path.join(ROOT, "paper_2609_19116_amd", "csrc", "kernels", "mps.hip")
-    base = "mps_wave_kernel" if kernel_name.startswith("mps_wave_kernel") else "mps_kernel"
+    base = kernel_name.split("<")[0]
+    src = os.path.join(ROOT, "paper_2609_19116_amd", "csrc", "kernels",
+                       "mps_fast.hip" if base.startswith("mps_fast") else "mps.hip")
     summ = os.path.join(ROOT, "profiles", f"{base}_c3_hbm_counters.md")
     if not os.path.exists(summ):
         return None

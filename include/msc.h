@@ -139,8 +139,13 @@ typedef struct {
                              chi_max) is run again from its start by the
                              workgroup kernel, so results follow chi_max.
                              0: 16 when lds_width is 0 and the circuit's
-                             calibrated noiseless run stays within bond 16,
-                             else off; -1: off; else 2..64.               */
+                             calibrated noiseless run stays within bond 16;
+                             for a run within bond 32 or 128, when large_side
+                             is 0 too and the circuit has no CS or CCZ, slots
+                             of that cap in the matrix-core kernels of such
+                             bonds (one shot per wavefront or per workgroup;
+                             engine_stats counts them as workgroup-kernel
+                             shots); else off; -1: off; else 2..64.       */
     const char* autotune_cache; /* path of an msc_autotune JSON file giving
                              the engine's tile shapes per precision and bucket
                              of theta sides; NULL: built-in shapes          */
@@ -234,7 +239,7 @@ typedef struct {
     int64_t overlapping;    /* overlapping vectors, summed over the updates  */
     int64_t sweeps;         /* Jacobi sweeps, summed                         */
     int64_t wave_slots;     /* shots in flight in the wavefront kernel (0:
-                               the workgroup kernel ran every shot)         */
+                               kernels of wider bonds ran every shot)       */
     int64_t wave_retries;   /* shots it handed to the workgroup kernel       */
 } msc_engine_stats;
 
