@@ -21,8 +21,8 @@
 // carries no FP32 rounding before it is stored).
 //
 // Measured against the wavefront kernel of mps.hip: 2^19 shots of the 49-qubit
-// circuit (p = 1e-3, FP32) 138.8 -> 81.1 ms a batch, 1000 shots (one shot's
-// latency) 36.3 -> 17.3 ms, 65536 17-qubit shots in FP64 64.7 -> 39.7 ms.  Per
+// circuit (p = 1e-3, FP32) 138.8 -> 76.9 ms a batch, 1000 shots (one shot's
+// latency) 36.3 -> 17.0 ms, 65536 17-qubit shots in FP64 64.7 -> 37.9 ms.  Per
 // batch the vector instructions fell from 6.0e10 to 2.3e10 and the LDS
 // instructions from 5.7e9 to 1.4e9; the matrix cores are busy 29 % of the
 // time.
@@ -439,10 +439,8 @@ __device__ __forceinline__ bool wave_update(const Trunc P, LW* L, const LTables*
 // Centre move (as move_fast) between sites with at most 16 vectors on the
 // bond, of at most 32 elements, and a neighbour of at most 32 elements per
 // vector: element 4 s + g of the vectors and of the neighbour's rows (columns)
-// in the lanes of vector q, which store both at the vector's rank.  Up to 16
-// elements (KS = 4) everything is loaded once and stays in registers; above
-// (KS = 0) the operands are read again for the stores.
-template <typename T, int KS, typename LW>
+// in the lanes of vector q, which store both at the vector's rank.
+template <typename T, typename LW>
 __device__ __forceinline__ bool wave_move(const Trunc P, LW* L, SiteView<T> A,
                                           SiteView<T> B, int k, int dir, ShotAcc& acc, int cl,
                                           int cm, int cr) {
@@ -456,8 +454,6 @@ __device__ __forceinline__ bool wave_move(const Trunc P, LW* L, SiteView<T> A,
     // element e of vector v, element x of the neighbour's part v
     const int xe = dir ? cm : 1, xv = dir ? 1 : len;
     const int ne = dir ? 1 : cm, nvs = dir ? w : 1;
-    constexpr int K = KS ? KS : 1;
-    T x0[K], x1[K], y0[K], y1[K];
     f64x4 re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
     const auto gram_step = [&](T a, T b, bool in) {
         const double xr = in ? static_cast<double>(a) : 0.0, xi = in ? static_cast<double>(b) : 0.0;
@@ -466,27 +462,11 @@ __device__ __forceinline__ bool wave_move(const Trunc P, LW* L, SiteView<T> A,
         re = mfma(xi, xi, re);
         im = mfma(-xi, xr, im);
     };
-    if constexpr (KS != 0) {
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const int e = 4 * s + g;
-            const uint32_t ix = q < nv && e < len ? q * xv + e * xe : 0;
-            const uint32_t in = q < nv && e < w ? q * nvs + e * ne : 0;
-            x0[s] = at(Xre, ix);
-            x1[s] = at(Xim, ix);
-            y0[s] = at(Nre, in);
-            y1[s] = at(Nim, in);
-        }
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-            if (4 * s < len) gram_step(x0[s], x1[s], q < nv && 4 * s + g < len);
-    } else {
 #pragma unroll 2
-        for (int e0 = 0; e0 < len; e0 += 4) {
-            const bool in = q < nv && e0 + g < len;
-            const uint32_t ix = in ? q * xv + (e0 + g) * xe : 0;
-            gram_step(at(Xre, ix), at(Xim, ix), in);
-        }
+    for (int e0 = 0; e0 < len; e0 += 4) {
+        const bool in = q < nv && e0 + g < len;
+        const uint32_t ix = in ? q * xv + (e0 + g) * xe : 0;
+        gram_step(at(Xre, ix), at(Xim, ix), in);
     }
     const double tau2 = P.tau * P.tau;
     const double tol = sizeof(T) == sizeof(double) ? static_cast<double>(len) * DBL_EPSILON
@@ -515,50 +495,133 @@ __device__ __forceinline__ bool wave_move(const Trunc P, LW* L, SiteView<T> A,
     const int ue = dir ? r : 1, uv = dir ? 1 : len;
     const int me = dir ? 1 : r, mv = dir ? w : 1;
     const double is = isq[0], sc = sq[0] * renorm;
-    if constexpr (KS != 0) {
-        if (rank[0] >= 0) {
+    // the stores permute (and, when vectors were dropped, pack) the
+    // tensors in place: every element is read before any is written
+    const auto rewrite = [&](gT* re_, gT* im_, int n, int se, int sv, int de, int dv, double f) {
+        T a[8], b[8];
 #pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const int e = 4 * s + g;
-                if (e < len) {
-                    const uint32_t ix = e * ue + rank[0] * uv;
-                    at(Xre, ix) = T(static_cast<double>(x0[s]) * is);
-                    at(Xim, ix) = T(static_cast<double>(x1[s]) * is);
-                }
-                if (e < w) {
-                    const uint32_t ix = e * me + rank[0] * mv;
-                    at(Nre, ix) = T(static_cast<double>(y0[s]) * sc);
-                    at(Nim, ix) = T(static_cast<double>(y1[s]) * sc);
-                }
-            }
+        for (int s = 0; s < 8; ++s) {
+            const int e = 4 * s + g;
+            const uint32_t ix = q < nv && e < n ? q * sv + e * se : 0;
+            a[s] = at(re_, ix);
+            b[s] = at(im_, ix);
         }
-    } else {
-        // the stores permute (and, when vectors were dropped, pack) the
-        // tensors in place: every element is read before any is written
-        const auto rewrite = [&](gT* re_, gT* im_, int n, int se, int sv, int de, int dv, double f) {
-            T a[8], b[8];
+        wave_order();
+        if (rank[0] >= 0) {
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
                 const int e = 4 * s + g;
-                const uint32_t ix = q < nv && e < n ? q * sv + e * se : 0;
-                a[s] = at(re_, ix);
-                b[s] = at(im_, ix);
-            }
-            wave_order();
-            if (rank[0] >= 0) {
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    const int e = 4 * s + g;
-                    if (e < n) {
-                        const uint32_t ix = e * de + rank[0] * dv;
-                        at(re_, ix) = T(static_cast<double>(a[s]) * f);
-                        at(im_, ix) = T(static_cast<double>(b[s]) * f);
-                    }
+                if (e < n) {
+                    const uint32_t ix = e * de + rank[0] * dv;
+                    at(re_, ix) = T(static_cast<double>(a[s]) * f);
+                    at(im_, ix) = T(static_cast<double>(b[s]) * f);
                 }
             }
-        };
-        rewrite(Xre, Xim, len, xe, xv, ue, uv, is);
-        rewrite(Nre, Nim, w, ne, nvs, me, mv, sc);
+        }
+    };
+    rewrite(Xre, Xim, len, xe, xv, ue, uv, is);
+    rewrite(Nre, Nim, w, ne, nvs, me, mv, sc);
+    if (lane == 0) L->chi[k + 1] = r;
+    wave_order();
+    return true;
+}
+
+// Selection among at most 8 vectors (as wave_select): lanes q and q + 8 both
+// answer for vector q mod 8, so the sums over a row count every vector twice
+// and are halved (exactly).
+template <typename LW>
+__device__ __forceinline__ Kept wave_select8(LW* L, double tau2, int capb, int& rank, double& isq,
+                                             double& sq, int nv) {
+    const int lane = op_lane(), q = lane & 15, g = lane >> 4, v = q & 7;
+    const uint32_t colmask = 0x00010001u << q;
+    const ldsd* nrm = L->nrm;
+    const double x = sel_norm(nrm[v]), y0 = sel_norm(nrm[g]), y1 = sel_norm(nrm[g + 4]);
+    const double mx = row_max(x);
+    const int rk = column_count(y0 > x || (y0 == x && g < v), colmask) +
+                   column_count(y1 > x || (y1 == x && g + 4 < v), colmask);
+    const bool above = v < nv && (x > tau2 * mx || rk == 0);
+    const bool keep = above && rk < capb;
+    Kept k;
+    k.want = __popc(static_cast<uint32_t>(__ballot(above)) & 0xFFu);
+    k.r = __popc(static_cast<uint32_t>(__ballot(keep)) & 0xFFu);
+    isq = rsqrt_nr(x);            // (of use where x is kept: never near 0)
+    sq = x * isq;
+    rank = keep ? rk : -1;
+    k.kept = 0.5 * row_sum(keep ? x : 0.0);
+    k.dropped = 0.5 * row_sum(keep ? 0.0 : x);
+    return k;
+}
+
+// Centre move (as wave_move) between bonds of at most 8: lane column q holds one
+// plane of vector q mod 8, the real one for q < 8, so one product of the 16
+// columns with themselves is the Gram matrix's four real parts (re = RR + II
+// and im = RI - IR, brought together by a rotation of the rows by 8), and
+// every load, scale and store handles one number instead of two.  49 qubits,
+// 2^19 shots: 80.6 -> 76.9 ms; 1000 17-qubit shots 2.83 -> 2.71 ms.  (Vectors of
+// up to 32 elements over such a bond gained nothing: the guards of their eight
+// loads cost a lone shot what the products saved.)
+template <typename T, typename LW>
+__device__ __forceinline__ bool wave_move8(const Trunc P, LW* L, SiteView<T> A, SiteView<T> B, int k,
+                                           int dir, ShotAcc& acc, int cl, int cm, int cr) {
+    typedef __attribute__((address_space(1))) T gT;
+    const int lane = op_lane(), q = lane & 15, g = lane >> 4, v = q & 7;
+    const int nv = cm, len = dir ? 2 * cl : 2 * cr, w = dir ? 2 * cr : 2 * cl;
+    gT* X = dir ? A.re : B.re;
+    gT* N = dir ? B.re : A.re;
+    // this lane's plane of either site
+    const uint32_t px = q < 8 ? 0 : static_cast<uint32_t>((dir ? A.im : B.im) - X);
+    const uint32_t pn = q < 8 ? 0 : static_cast<uint32_t>((dir ? B.im : A.im) - N);
+    const int xe = dir ? cm : 1, xv = dir ? 1 : len;
+    const int ne = dir ? 1 : cm, nvs = dir ? w : 1;
+    constexpr int KS = 4;
+    T x[KS], y[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int e = 4 * s + g;
+        x[s] = at(X, v < nv && e < len ? px + v * xv + e * xe : 0);
+        y[s] = at(N, v < nv && e < w ? pn + v * nvs + e * ne : 0);
+    }
+    f64x4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+        if (4 * s < len) {
+            const double t = v < nv && 4 * s + g < len ? static_cast<double>(x[s]) : 0.0;
+            d = mfma(t, t, d);
+        }
+    // rows g and g + 4 of columns q < 8
+    const double re0 = d[0] + dpp_move<0x128>(d[2]), re1 = d[1] + dpp_move<0x128>(d[3]);
+    const double im0 = dpp_move<0x128>(d[0]) - d[2], im1 = dpp_move<0x128>(d[1]) - d[3];
+    const double tau2 = P.tau * P.tau;
+    const double tol = sizeof(T) == sizeof(double) ? static_cast<double>(len) * DBL_EPSILON
+                                                   : 8.0 * static_cast<double>(FLT_EPSILON);
+    ldsd* nrm = L->nrm;
+    if (q < 8 && g == (q & 3)) nrm[q] = (q & 4) ? re1 : re0;
+    wave_order();
+    const double nq = nrm[v];
+    const double total = 0.5 * row_sum(nq), floor2 = 1e-4 * tau2 * total;
+    const double a0 = nrm[g], a1 = nrm[g + 4];
+    const auto overlaps = [&](double a, double re, double im, int p) {
+        return p < q && q < 8 && a > floor2 && nq > floor2 &&
+               re * re + im * im > tol * tol * a * nq;
+    };
+    if (__ballot(overlaps(a0, re0, im0, g) || overlaps(a1, re1, im1, g + 4)) != 0ull) return false;
+    const int capb = P.cap;
+    int rank;
+    double is, sc;
+    const Kept kp = wave_select8(L, tau2, capb, rank, is, sc, nv);
+    const int r = kp.r;
+    acc.disc += kp.dropped;
+    if (kp.dropped > 1e-12 * total && r == capb) acc.status |= MSC_SHOT_CHI_CAP;
+    sc *= rsqrt_nr(kp.kept);
+    const int ue = dir ? r : 1, uv = dir ? 1 : len;
+    const int me = dir ? 1 : r, mv = dir ? w : 1;
+    if (rank >= 0) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int e = 4 * s + g;
+            if (e < len) at(X, px + e * ue + rank * uv) = T(static_cast<double>(x[s]) * is);
+            if (e < w) at(N, pn + e * me + rank * mv) = T(static_cast<double>(y[s]) * sc);
+        }
     }
     if (lane == 0) L->chi[k + 1] = r;
     wave_order();
@@ -1438,8 +1501,9 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LW* L, const LTables*
                     }
                 } else {
                     const SiteView<T> A = site(a), B = site(a + 1);
-                    fast = max(cl, cr) <= 8 ? wave_move<T, 4>(trunc, L, A, B, a, b, acc, cl, cm, cr)
-                                            : wave_move<T, 0>(trunc, L, A, B, a, b, acc, cl, cm, cr);
+                    fast = max(max(cl, cr), cm) <= 8
+                               ? wave_move8<T>(trunc, L, A, B, a, b, acc, cl, cm, cr)
+                               : wave_move<T>(trunc, L, A, B, a, b, acc, cl, cm, cr);
                 }
                 if (!fast) {
                     twosite = true;
