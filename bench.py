@@ -630,7 +630,7 @@ def shot_kernel(wave_slots: int, wave_chi: int, lds_width: int, chi_peak: int) -
     if wave_slots:
         return f"mps_{'fast_' if wave_chi <= 16 else ''}wave_kernel<float, false>"
     if wave_chi == 0 and lds_width == 0 and chi_peak <= 128:
-        return f"mps_fast_{'mid' if chi_peak <= 32 else 'group'}_kernel<float, false>"
+        return f"mps_fast_{'mid' if chi_peak <= 32 else 'group'}_kernel<float>"
     return f"mps_kernel<float,{64 if lds_width == 64 else 32}>"
 
 

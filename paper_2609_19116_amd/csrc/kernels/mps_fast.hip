@@ -23,8 +23,8 @@
 // Measured against the wavefront kernel of mps.hip: 2^19 shots of the 49-qubit
 // circuit (p = 1e-3, FP32) 138.8 -> 76.9 ms a batch, 1000 shots (one shot's
 // latency) 36.3 -> 17.0 ms, 65536 17-qubit shots in FP64 64.7 -> 37.9 ms.  Per
-// batch the vector instructions fell from 6.0e10 to 2.3e10 and the LDS
-// instructions from 5.7e9 to 1.4e9; the matrix cores are busy 29 % of the
+// batch the vector instructions fell from 6.0e10 to 2.2e10 and the LDS
+// instructions from 5.7e9 to 1.4e9; the matrix cores are busy 26 % of the
 // time.
 #include <hip/hip_runtime.h>
 
