@@ -40,7 +40,15 @@ constexpr int CT = 256;
 constexpr int K = kCampsK;
 constexpr int NR = 2 * kMaxSites;
 constexpr int kMaxSweeps = 60;
-constexpr double kOrtho = 3e-15;   // |x^H y| / (|x| |y|) of vectors that count as orthogonal
+constexpr double kOrtho = 1e-15;   // |x^H y| / (|x| |y|) of vectors that count as orthogonal
+// (sigma / sigma_max)^2 below which a column is the rounding of the others:
+// left as it is, so what it has along a kept column is lost with it.  It may
+// not follow the caller's truncation threshold, since that loss is of first
+// order in the column's norm: with the floor at a tenth of the threshold P_acc
+// was off by 2e-8 at tau_trunc = 0.01 and by 4e-4 at 0.03 where no Schmidt
+// value lay below it.  Without a floor such columns overlap with everything and
+// nearly every factorisation needs a round-robin sweep.
+constexpr double kNoise2 = 1e-30;
 
 // scratch layout (doubles) of one slot
 constexpr int64_t oW = 0;                     // 2 x (2K x K), column-major, ld 2K
@@ -136,7 +144,7 @@ struct WV {
 struct PairLds {
     double nrm[kWaveCols], gre[kWaveCols], gim[kWaveCols];
     int cnt[kWaveCols], mate[kWaveCols];
-    int over;
+    int over, rotated;
 };
 typedef __attribute__((address_space(3))) PairLds LPair;
 
@@ -205,15 +213,15 @@ __device__ __forceinline__ void rr_pair(int i, int t, int m, int& p, int& q) {
 // sweeps used (-1: no convergence).
 //
 // In LDS, each sweep starts from the Gram matrix of the columns on FP64 MFMA:
-// pairs with |x^H y| <= kOrtho |x| |y| count as orthogonal, and
-// columns below a tenth of the threshold thr * sigma_max that the caller drops
-// by as zero.  When every overlapping column has exactly one mate, which is
-// the usual case, all pairs rotate in one step; else one round-robin sweep
-// by wavefront 0.  A round-robin sweep over 32 columns is 31 dependent steps
-// and needed a second one to find nothing left: 256 49-qubit shots (one
-// shot's latency) 185 -> 121 ms.  The columns' squared norms are left in
-// J.nrm.
-__device__ int jacobi_cols(const WV& w, int len, int nv, double thr, int* s_flag, LPair* J) {
+// pairs with |x^H y| <= kOrtho |x| |y| count as orthogonal, and columns at the
+// rounding of the largest one (kNoise2) as zero.  When every overlapping column
+// has exactly one mate, which is the usual case, all pairs rotate in one step;
+// else one round-robin sweep by wavefront 0, whose own sums decide: the columns
+// are orthogonal if it rotates nothing.  A round-robin sweep over 32 columns is
+// 31 dependent steps and needed a second one to find nothing left: 256 49-qubit
+// shots (one shot's latency) 185 -> 121 ms.  The columns' squared norms are
+// left in J.nrm.
+__device__ int jacobi_cols(const WV& w, int len, int nv, int* s_flag, LPair* J) {
     const int tid = threadIdx.x;
     if (w.wave) {
         const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -247,7 +255,7 @@ __device__ int jacobi_cols(const WV& w, int len, int nv, double thr, int* s_flag
             __syncthreads();
             if (floor2 < 0.0) {
                 const int lane = tid & 63;
-                floor2 = 1e-2 * thr * thr * wave_sum(lane < 16 * nvt ? (double)J->nrm[lane] : 0.0);
+                floor2 = kNoise2 * wave_max(lane < 16 * nvt ? (double)J->nrm[lane] : 0.0);
             }
             int any = 0;
             if (wid < nvt)
@@ -290,16 +298,20 @@ __device__ int jacobi_cols(const WV& w, int len, int nv, double thr, int* s_flag
                 int G = 64;
                 while (G > 1 && G * np > 64) G >>= 1;
                 const int g = tid / G, l = tid - g * G;
+                bool rotated = false;
                 for (int t = 0; t < m - 1; ++t) {
                     if (g < np) {
                         int p, q;
                         rr_pair(g, t, m, p, q);
-                        jacobi_pair(w, len, nv, p, q, G, l);
+                        rotated |= jacobi_pair(w, len, nv, p, q, G, l);
                     }
                     wave_sync();
                 }
+                const int r = __ballot(rotated) != 0ull;
+                if (tid == 0) J->rotated = r;
             }
             __syncthreads();
+            if (over >= 2 && !J->rotated) return sweep + 1;
         }
         return -1;
     }
@@ -465,7 +477,7 @@ __device__ __forceinline__ bool trivial_move(const Res& R, const Ctl& c, int k, 
     store_diagonal(re, nrm);
     wave_order();
     const double nq = nrm[q];
-    const double floor2 = 1e-2 * tau * tau * row_sum(nq);
+    const double floor2 = kNoise2 * row_max(nq);
     bool over = false;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -533,7 +545,7 @@ __device__ void move_right(const Res& R, const Ctl& c, int k, double tau) {
         wi[b * ldw + row] = ai[row * cr + b];
     }
     __syncthreads();
-    note_sweeps(c, jacobi_cols(w, len, cr, tau, c.flag, c.pairs));
+    note_sweeps(c, jacobi_cols(w, len, cr, c.flag, c.pairs));
     const int r = select_cols(w, len, cr, tau, c.sg, c.keep, c.red, c.pairs);
     double *Ar = R.re(k), *Ai = R.im(k);
     for (int e = tid; e < len * r; e += CT) {
@@ -593,7 +605,7 @@ __device__ void move_left(const Res& R, const Ctl& c, int k, double tau) {
         wi[a * ldw + x] = -ai[a * len + x];
     }
     __syncthreads();
-    note_sweeps(c, jacobi_cols(w, len, cl, tau, c.flag, c.pairs));
+    note_sweeps(c, jacobi_cols(w, len, cl, c.flag, c.pairs));
     const int r = select_cols(w, len, cl, tau, c.sg, c.keep, c.red, c.pairs);
     double *Ar = R.re(k), *Ai = R.im(k);
     for (int e = tid; e < r * len; e += CT) {
@@ -865,7 +877,7 @@ __device__ bool apply_sum(const Res& R, const Ctl& c, Frame F, int r, double alr
             __syncthreads();
             break;
         }
-        note_sweeps(c, jacobi_cols(w, len, D, 1e-14, c.flag, c.pairs));
+        note_sweeps(c, jacobi_cols(w, len, D, c.flag, c.pairs));
         const int rn = select_cols(w, len, D, 1e-14, c.sg, c.keep, c.red, c.pairs);
         if (rn > K) return false;     // cannot happen: rn <= D <= K
         double *Ar = R.re(k), *Ai = R.im(k);
@@ -1205,7 +1217,7 @@ __global__ __launch_bounds__(CT) void camps_kernel(CampsArgs P) {
                 }
                 __syncthreads();
                 // split D theta: A_k = U, A_{k+1} = S V^dag
-                note_sweeps(C, jacobi_cols(w, m, nn, tau, &s_flag, C.pairs));
+                note_sweeps(C, jacobi_cols(w, m, nn, &s_flag, C.pairs));
                 const int rr = select_cols(w, m, nn, tau, s_sg, s_keep, s_red, C.pairs);
                 double *Ar = R.re(k), *Ai = R.im(k), *Br = R.re(k + 1), *Bi = R.im(k + 1);
                 for (int e = tid; e < m * rr; e += CT) {
