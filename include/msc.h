@@ -140,12 +140,13 @@ typedef struct {
                              workgroup kernel, so results follow chi_max.
                              0: 16 when lds_width is 0 and the circuit's
                              calibrated noiseless run stays within bond 16;
-                             for a run within bond 32 or 128, when large_side
-                             is 0 too and the circuit has no CS or CCZ, slots
-                             of that cap in the matrix-core kernels of such
-                             bonds (one shot per wavefront or per workgroup;
-                             engine_stats counts them as workgroup-kernel
-                             shots); else off; -1: off; else 2..64.       */
+                             for a run within bond 32 or 128 and within
+                             chi_max, when large_side is 0 too and the circuit
+                             has no CS or CCZ, slots of that cap in the
+                             matrix-core kernels of such bonds (one shot per
+                             wavefront or per workgroup; engine_stats counts
+                             them as workgroup-kernel shots); else off; -1:
+                             off; else 2..64.                             */
     const char* autotune_cache; /* path of an msc_autotune JSON file giving
                              the engine's tile shapes per precision and bucket
                              of theta sides; NULL: built-in shapes          */

@@ -505,13 +505,19 @@ static int enqueue_shots(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, 
                          const PrefixCk* pk, const int64_t* n_dev, double* surv,
                          const int64_t* perm_in);
 
-// Whether a circuit's shots take the matrix-core kernels.  Not those with
-// controlled-S or CCZ gates: they leave sets of more than two overlapping
-// vectors with equal singular values, whose basis after a factorisation, and
-// with it which later centre moves find overlaps (the records' n2q and flops),
-// follows the last bit of the rotations' order and rounding.  Their records
-// stay what the round-robin kernels compute.
-static bool fast_path(const msc_circuit* c) { return c->pair_spectra; }
+// Whether a circuit's shots take the matrix-core kernels under a bond cap of
+// chi_max.  Not those with controlled-S or CCZ gates: they leave sets of more
+// than two overlapping vectors with equal singular values, whose basis after a
+// factorisation, and with it which later centre moves find overlaps (the
+// records' n2q and flops), follows the last bit of the rotations' order and
+// rounding.  Nor runs whose cap already cuts the noiseless run: among equal
+// singular values the basis then decides what is dropped, that is P_acc and the
+// discarded weight (81 qubits, bond 64, chi_max 32, FP32, the largest of 64
+// shots: 1.9 in the round-robin kernels, 17.5 here).  The records of both stay
+// what the round-robin kernels compute.
+static bool fast_path(const msc_circuit* c, int chi_max) {
+    return c->pair_spectra && c->noiseless.chi_peak <= chi_max;
+}
 
 // The wavefront kernel's pass over the shots (slots of bond cap wave_chi,
 // one shot per wavefront, shots taken from a shared counter), then the shots
@@ -523,7 +529,7 @@ static int enqueue_wave(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, i
                         const uint8_t* pauli, const int64_t* shot_idx, msc_shot_result* out,
                         int ck_mode, const PrefixCk* pk, const int64_t* n_dev, double* surv) {
     const int precision = cfg.precision, cw = cfg.wave_chi;
-    const bool fast = fast_path(c) && (cw <= kFastWaveBond || cfg.fast_wide);
+    const bool fast = fast_path(c, cfg.chi_max) && (cw <= kFastWaveBond || cfg.fast_wide);
     const FastKernel fk = fast_kernel(cw);
     const int per_wg = fast ? fk.teams : kWaveTeams;
     Layout L = make_layout(c->n, cw, 2 * cw);
@@ -1036,7 +1042,7 @@ static int sim_cfg(const msc_sim_opts* o, const msc_circuit* c, RunCfg* cfg) {
              c->noiseless.chi_peak <= kAutoWaveChi)
         wc = kAutoWaveChi;
     else if (o->wave_chi == 0 && o->lds_width == 0 && o->large_side == 0 && c && c->calibrated &&
-             fast_path(c) && c->noiseless.chi_peak <= kFastGroupBond) {
+             fast_path(c, o->chi_max) && c->noiseless.chi_peak <= kFastGroupBond) {
         // wider circuits: the matrix-core kernels of the next caps (49 qubits
         // on the snake layout, bond 32, 20000 shots: 79.7 ms in the workgroup
         // kernel, 38.6 here; 256 shots of the 81-qubit patch, bond 64: 1159 ms
