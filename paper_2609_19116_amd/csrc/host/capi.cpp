@@ -541,11 +541,12 @@ static int enqueue_wave(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, i
     teams = std::max<int64_t>(1, std::min<int64_t>(teams, n));
     const int grid = static_cast<int>((teams + per_wg - 1) / per_wg);
     const int64_t slots = static_cast<int64_t>(grid) * per_wg;
+    const int64_t scratch_stride = fast ? fast_scratch(cw) : L.scratch;
     const size_t tsize = precision == MSC_FP64 ? sizeof(double) : sizeof(float);
     void *arena, *scratch, *dcap, *doff, *dhalf, *dperm, *dctr, *dlist;
     int rc;
     if ((rc = ctx_buf(ctx, "w_arena", static_cast<size_t>(slots) * L.slot_elems * tsize, &arena))) return rc;
-    if ((rc = ctx_buf(ctx, "w_scratch", static_cast<size_t>(slots) * L.scratch * sizeof(double), &scratch))) return rc;
+    if ((rc = ctx_buf(ctx, "w_scratch", static_cast<size_t>(slots) * scratch_stride * sizeof(double), &scratch))) return rc;
     if ((rc = ctx_buf(ctx, "w_cap", L.cap.size() * sizeof(int32_t), &dcap))) return rc;
     if ((rc = ctx_buf(ctx, "w_off", L.off.size() * sizeof(int64_t), &doff))) return rc;
     if ((rc = ctx_buf(ctx, "w_half", L.half.size() * sizeof(int64_t), &dhalf))) return rc;
@@ -570,7 +571,7 @@ static int enqueue_wave(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, i
     a.site_half = static_cast<const int64_t*>(dhalf);
     a.cap = static_cast<const int32_t*>(dcap);
     a.scratch = static_cast<double*>(scratch);
-    a.scratch_stride = L.scratch;
+    a.scratch_stride = scratch_stride;
     a.next = static_cast<unsigned long long*>(dctr);
     a.retry_count = reinterpret_cast<int32_t*>(static_cast<char*>(dctr) + 8);
     a.retry_list = static_cast<int64_t*>(dlist);

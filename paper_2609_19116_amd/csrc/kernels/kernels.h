@@ -142,9 +142,16 @@ constexpr int kWaveTeams = 4;      // shots per workgroup of the wavefront kerne
 // The same on the matrix cores (mps_fast.hip), by the slots' bond cap: one shot
 // per wavefront up to kFastMidBond (four per workgroup up to kFastWaveBond,
 // kMidTeams above), one per workgroup of kGroupWaves wavefronts up to
-// kFastGroupBond.  The scratch holds 2 side (2 side + 1) doubles per slot, side
-// = 2 cap rounded up to 16, at least 32.
+// kFastGroupBond.
 constexpr int kFastWaveBond = 16, kFastMidBond = 32, kFastGroupBond = 128;
+// Scratch (doubles) that these kernels need per slot of bond cap `cap`: the
+// vectors of the widest factorisation (2 cap of them, of 2 cap elements, both
+// padded to 16) at a stride of twice their length and one, and theta's copy at
+// the same stride.  Kernel and allocation both take it from here.
+constexpr int64_t fast_scratch(int cap) {
+    const int64_t side = cap <= kFastWaveBond ? 32 : (2ll * cap + 15) / 16 * 16;
+    return 2 * side * (2 * side + 1);
+}
 constexpr int kMidTeams = 7, kGroupWaves = 8;
 struct FastKernel {
     int teams;           // shots per workgroup

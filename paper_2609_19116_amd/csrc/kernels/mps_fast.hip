@@ -1842,10 +1842,9 @@ hipError_t launch_mps_fast(int precision, int cap, const MpsArgs& a, int grid, h
     static_assert(sizeof(WaveLds) * NW + sizeof(TableLds) <= 160 * 1024 / 3, "three workgroups per CU");
     static_assert(sizeof(MidLds) * kMidTeams + sizeof(TableLds) <= 160 * 1024, "LDS of one CU");
     static_assert(sizeof(GroupLds) + sizeof(TableLds) <= 160 * 1024, "LDS of one CU");
-    // vectors and theta's copy of the widest factorisation, in the scratch
-    const int64_t side = cap <= kFastWaveBond ? 32 : 2 * ((cap + 7) & ~7);
+    static_assert(2 * kStash <= fast_scratch(1), "theta and the vectors of a cap-16 slot");
     if (!a.next || !a.retry_count || !a.retry_list || a.calibrate || a.state || cap < 1 ||
-        cap > kFastGroupBond || a.scratch_stride < 2 * side * (2 * side + 1))
+        cap > kFastGroupBond || a.scratch_stride < fast_scratch(cap))
         return hipErrorInvalidValue;
     const auto go = [&](auto kernel, int nt) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(nt), 0, s, a);

@@ -54,3 +54,23 @@ def test_cap_below_the_noiseless_bond_keeps_the_workgroup_kernel(ctx, chi_max, p
     assert np.any(a["status"] & msc.SHOT_CHI_CAP)
     for f in FIELDS:
         assert np.array_equal(a[f], b[f]), f
+
+
+@pytest.mark.parametrize("precision", [MSC_FP64, MSC_FP32])
+@pytest.mark.parametrize("prefix", [False, True])
+def test_every_cap_that_holds_the_bond_gives_the_same_records(ctx, prefix, precision):
+    # slots of any cap from the noiseless bond (64) on: the cap is where a slot
+    # ends, not part of a result (66 to 124: theta sides that are no multiple
+    # of 16)
+    c = _circuit(ctx, "c4")
+    assert c.noiseless()["chi_peak"] == 64
+    off, ch, pa = to_dev(*msc.sample_faults(c, 0x5EED0212, 0, 3,
+                                            weights=np.array([0, 1, 2], dtype=np.int32)))
+    kw = dict(precision=precision, prefix=prefix)
+    ref = results_numpy(msc.simulate(ctx, c, off, ch, pa, **kw))
+    assert not np.any(ref["status"] & msc.SHOT_CHI_CAP)
+    for chi_max in (64, 65, 66, 74, 82, 91, 100, 108, 116, 124, 127, 128, 129):
+        say(f"c4 chi_max={chi_max} prefix={prefix} precision={precision}")
+        a = results_numpy(msc.simulate(ctx, c, off, ch, pa, chi_max=chi_max, **kw))
+        for f in FIELDS:
+            assert np.array_equal(a[f], ref[f]), (f, chi_max)
