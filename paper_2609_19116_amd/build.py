@@ -7,6 +7,7 @@ paper_2609_19116_amd/libmsc.so.  Run ``python -m paper_2609_19116_amd.build``.
 from __future__ import annotations
 
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -44,11 +45,47 @@ COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang",
           "-packed-fp32-ops"]
 
+# Kernels whose registers the build checks: source, name, and the wavefronts
+# per SIMD that the launch counts on, with no vector register spilled.
+RESOURCES = {
+    "camps.hip": {"camps_kernel": 2},
+}
+REPORT = ["-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics"]
+
+
+def kernel_resources(report: str) -> dict:
+    """Per kernel (mangled name) the figures of the compiler's resource report."""
+    out, cur = {}, None
+    for ln in report.splitlines():
+        m = re.search(r"remark:\s*(.+?):\s*(\S+)\s*\[-Rpass-analysis=kernel-resource-usage\]", ln)
+        if not m:
+            continue
+        if m[1] == "Function Name":
+            cur = out[m[2]] = {}
+        elif cur is not None:
+            cur[m[1]] = int(m[2]) if m[2].isdigit() else m[2]
+    return out
+
+
+def check_resources(source: str, report: str) -> None:
+    """Raise if a kernel of RESOURCES[source] spills vector registers, has
+    fewer resident wavefronts than its launch counts on, or is not reported."""
+    seen = kernel_resources(report)
+    for name, waves in RESOURCES.get(source, {}).items():
+        found = {k: r for k, r in seen.items() if re.search(rf"\d{name}(?![a-z_])", k)}
+        if not found:
+            raise RuntimeError(f"{source}: no resource report of {name}")
+        for k, r in found.items():
+            if r["VGPRs Spill"] > 0 or r["Occupancy [waves/SIMD]"] < waves:
+                raise RuntimeError(f"{source}: {k} needs {waves} wavefronts per SIMD and no "
+                                   f"spilled vector registers, the compiler reports {r}")
+
 
 def _compile(src: Path) -> Path:
     obj = BUILD / (src.stem + (".hip.o" if src.suffix == ".hip" else ".o"))
     if src.suffix == ".hip":
-        cmd = [HIPCC, "-x", "hip", *DEVICE, *COMMON, "-c", str(src), "-o", str(obj)]
+        cmd = [HIPCC, "-x", "hip", *DEVICE, *COMMON, *(REPORT if src.name in RESOURCES else []),
+               "-c", str(src), "-o", str(obj)]
     else:
         # host-only sources still include the HIP runtime headers
         cmd = [HIPCC, "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", *COMMON, "-c", str(src),
@@ -58,9 +95,10 @@ def _compile(src: Path) -> Path:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     if r.stderr.strip():
         warn = [ln for ln in r.stderr.splitlines()
-                if "packed-fp32-ops" not in ln and ln.strip()]
+                if "packed-fp32-ops" not in ln and "remark:" not in ln and ln.strip()]
         if warn:
             sys.stderr.write("\n".join(warn) + "\n")
+    check_resources(src.name, r.stderr)
     return obj
 
 

@@ -911,7 +911,12 @@ __device__ bool apply_sum(const Res& R, const Ctl& c, Frame F, int r, double alr
 
 }  // namespace
 
-__global__ __launch_bounds__(CT) void camps_kernel(CampsArgs P) {
+// Two workgroups per CU, as the LDS allows (67 of 160 KB): a shot is a chain of
+// barriers and dependent loads, so a second shot on the CU costs the first
+// nearly nothing.  4096 survivors of the 49-qubit circuit: 314 ms at one per CU
+// (273 registers), 191 at two (256, nothing spilled; 178 since kNoise2); 256 of
+// them, one per CU: 82.7 and 82.1 (74).
+__global__ __launch_bounds__(CT, 2) void camps_kernel(CampsArgs P) {
     __shared__ uint64_t s_x[NR * 2], s_z[NR * 2];
     __shared__ uint8_t s_ph[NR];
     __shared__ uint8_t s_laste[kMaxSites];
