@@ -287,9 +287,8 @@ def main() -> int:
     achieved = float(np.mean(flops)) / (float(np.mean(sim_ms)) * 1e-3) / 1e12
     # which shot kernel ran the steps (the instance without checkpoint
     # recording and segment reach, which the timed steps do not use)
-    wave_slots = ctxs[0].engine_stats()["wave_slots"]
-    kernel_name = shot_kernel(wave_slots, args.wave_chi, args.lds_width,
-                              circ.noiseless()["chi_peak"])
+    shot_stats = ctxs[0].engine_stats()
+    kernel_name = shot_kernel(shot_stats, args.lds_width)
     achieved_job = sum(flops) / wall / 1e12
     sweeps = sum(st["sweeps"] for st in sts)
     log(f"steps={args.steps} wall={wall:.3f}s value={value:.1f} shots/s survivors={n_surv} "
@@ -347,7 +346,7 @@ def main() -> int:
                       "prescreen_mean": float(np.mean(screen_ms)),
                       "sample_mean": float(np.mean(sample_ms))},
         "roofline": {"bound": "alu",
-                     "kernel": kernel_name, "slots": wave_slots or None,
+                     "kernel": kernel_name, "slots": shot_stats["slots"],
                      "achieved": achieved, "peak": PEAK_VALU, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_VALU, "traffic": measured_traffic(layout_key, kernel_name),
                      "launch_ms": float(np.mean(sim_ms)),
@@ -615,23 +614,18 @@ def workloads_17q(msc, ctx) -> dict:
             line[pname] = {"ms": t, "shots_per_s": n17 / (t * 1e-3),
                            "gate_updates_per_s": float(r17["n2q"].sum()) / (t * 1e-3),
                            "chi_peak": int(r17["chi_peak"].max()),
-                           "kernel": shot_kernel(ctx.engine_stats()["wave_slots"], 0, 0,
-                                                 c17.noiseless()["chi_peak"]).split("<")[0]}
+                           "kernel": ctx.engine_stats()["shot_kernel"]}
         lines[name] = line
         del o17, ch17, pa17
     return lines
 
 
-def shot_kernel(wave_slots: int, wave_chi: int, lds_width: int, chi_peak: int) -> str:
-    """The shot kernel that FP32 runs of a circuit without CS and CCZ take
-    (chi_peak: bond of its noiseless run): one shot per wavefront up to bond
-    16 (wave_slots > 0) and 32, one per workgroup on the matrix cores up to
-    128, the general workgroup kernel otherwise."""
-    if wave_slots:
-        return f"mps_{'fast_' if wave_chi <= 16 else ''}wave_kernel<float, false>"
-    if wave_chi == 0 and lds_width == 0 and chi_peak <= 128:
-        return f"mps_fast_{'mid' if chi_peak <= 32 else 'group'}_kernel<float>"
-    return f"mps_kernel<float,{64 if lds_width == 64 else 32}>"
+def shot_kernel(stats: dict, lds_width: int) -> str:
+    """The FP32 instance of the shot kernel that engine_stats names."""
+    name = stats["shot_kernel"]
+    args = {"mps_kernel": f",{64 if lds_width == 64 else 32}", "mps_wave_kernel": ", false",
+            "mps_fast_wave_kernel": ", false"}
+    return f"{name}<float{args.get(name, '')}>"
 
 
 def measured_traffic(layout_key: str, kernel_name: str):

@@ -144,9 +144,9 @@ typedef struct {
                              chi_max, when large_side is 0 too and the circuit
                              has no CS or CCZ, slots of that cap in the
                              matrix-core kernels of such bonds (one shot per
-                             wavefront or per workgroup; engine_stats counts
-                             them as workgroup-kernel shots); else off; -1:
-                             off; else 2..64.                             */
+                             wavefront or per workgroup); else off; -1: off;
+                             else 2..64.  msc_ctx_shot_stats says which
+                             kernel ran.                                  */
     const char* autotune_cache; /* path of an msc_autotune JSON file giving
                              the engine's tile shapes per precision and bucket
                              of theta sides; NULL: built-in shapes          */
@@ -239,12 +239,33 @@ typedef struct {
                                the slot's workspace                          */
     int64_t overlapping;    /* overlapping vectors, summed over the updates  */
     int64_t sweeps;         /* Jacobi sweeps, summed                         */
-    int64_t wave_slots;     /* shots in flight in the wavefront kernel (0:
-                               kernels of wider bonds ran every shot)       */
-    int64_t wave_retries;   /* shots it handed to the workgroup kernel       */
+    int64_t wave_slots;     /* shots in flight in the kernels of bond 16 and
+                               of an explicit wave_chi (0: kernels of wider
+                               bonds ran every shot)                        */
+    int64_t wave_retries;   /* shots they handed to the workgroup kernel     */
 } msc_engine_stats;
 
 int msc_ctx_engine_stats(msc_ctx* ctx, msc_engine_stats* out);
+
+/* Which shot kernel took the shots of the context's last msc_simulate or
+   msc_run_batch call.                                                     */
+enum msc_shot_kernel {
+    MSC_SHOT_KERNEL_NONE = 0,
+    MSC_SHOT_KERNEL_WORKGROUP = 1,   /* one shot per workgroup              */
+    MSC_SHOT_KERNEL_WAVE = 2,        /* one per wavefront, vector ALUs       */
+    MSC_SHOT_KERNEL_FAST_WAVE = 3,   /* matrix cores, one per wavefront: bond */
+    MSC_SHOT_KERNEL_FAST_MID = 4,    /*   at most 16, at most 32             */
+    MSC_SHOT_KERNEL_FAST_GROUP = 5   /* matrix cores, one per workgroup, 128 */
+};
+typedef struct {
+    int32_t kernel;         /* msc_shot_kernel                               */
+    int32_t slot_chi;       /* bond cap of its slots                         */
+    int64_t slots;          /* shots in flight                               */
+    int64_t retries;        /* shots that outgrew their slot and were run
+                               again from their start by the workgroup kernel */
+} msc_shot_stats;
+
+int msc_ctx_shot_stats(msc_ctx* ctx, msc_shot_stats* out);
 
 /* ---------------------------------------------------------------------- */
 /* Circuit: parse + compile on the host (no GPU needed).                  */

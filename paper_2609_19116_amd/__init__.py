@@ -14,8 +14,8 @@ import numpy as np
 
 from ._lib import (BatchStats, EngineStats, TuneEntry, MSC_BF16X3, MSC_FP32, MSC_FP64, MSC_STAT_PACC,  # noqa: F401
                    MSC_ORDER_COST_MOVE, MSC_ORDER_COST_PSWAP, MSC_ORDER_COST_TWOSITE,
-                   MSC_STAT_PLE, SEGMENT_DTYPE, SHOT_CHI_CAP, SHOT_DONE, SHOT_DTYPE, SHOT_NOCONV, SHOT_MPS_RERUN,
-                   SHOT_REJECTED, CircuitInfo, Estimate, Interval, MscError, SimOpts, _check,
+                   MSC_STAT_PLE, SEGMENT_DTYPE, SHOT_CHI_CAP, SHOT_DONE, SHOT_DTYPE, SHOT_KERNELS, SHOT_NOCONV, SHOT_MPS_RERUN,
+                   SHOT_REJECTED, CircuitInfo, Estimate, Interval, MscError, ShotStats, SimOpts, _check,
                    _ptr, lib)
 
 __all__ = ["Ctx", "Circuit", "sample_faults", "sample_faults_device", "prescreen", "simulate",
@@ -58,10 +58,15 @@ class Ctx:
         return lib().msc_ctx_last_kernel_ms(self.h, which.encode())
 
     def engine_stats(self) -> dict:
-        """msc_ctx_engine_stats: the large-update engine in the last shot run."""
-        st = EngineStats()
+        """msc_ctx_engine_stats: the large-update engine in the last shot run;
+        with msc_ctx_shot_stats under "shot_kernel" (the kernel's name),
+        "slot_chi", "slots" and "slot_retries"."""
+        st, sh = EngineStats(), ShotStats()
         _check(lib().msc_ctx_engine_stats(self.h, C.byref(st)))
-        return {f: getattr(st, f) for f, _ in EngineStats._fields_}
+        _check(lib().msc_ctx_shot_stats(self.h, C.byref(sh)))
+        return {**{f: getattr(st, f) for f, _ in EngineStats._fields_},
+                "shot_kernel": SHOT_KERNELS[sh.kernel], "slot_chi": sh.slot_chi,
+                "slots": sh.slots, "slot_retries": sh.retries}
 
 
 class Circuit:

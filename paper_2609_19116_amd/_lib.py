@@ -85,6 +85,16 @@ class EngineStats(C.Structure):
                 ("sweeps", C.c_int64), ("wave_slots", C.c_int64), ("wave_retries", C.c_int64)]
 
 
+class ShotStats(C.Structure):
+    _fields_ = [("kernel", C.c_int32), ("slot_chi", C.c_int32), ("slots", C.c_int64),
+                ("retries", C.c_int64)]
+
+
+# the kernels' names, by MSC_SHOT_KERNEL_*
+SHOT_KERNELS = (None, "mps_kernel", "mps_wave_kernel", "mps_fast_wave_kernel",
+                "mps_fast_mid_kernel", "mps_fast_group_kernel")
+
+
 class TuneEntry(C.Structure):
     _fields_ = [("bucket", C.c_int32), ("side", C.c_int32), ("batch", C.c_int32),
                 ("rows", C.c_int32), ("b", C.c_int32), ("gram", C.c_int32),
@@ -118,6 +128,7 @@ _SIGS = {
     "msc_ctx_destroy": (None, [_P]),
     "msc_ctx_last_kernel_ms": (C.c_double, [_P, C.c_char_p]),
     "msc_ctx_engine_stats": (C.c_int, [_P, C.POINTER(EngineStats)]),
+    "msc_ctx_shot_stats": (C.c_int, [_P, C.POINTER(ShotStats)]),
     "msc_circuit_load": (C.c_int, [C.c_char_p, C.c_size_t, _P, C.POINTER(_P)]),
     "msc_circuit_get_info": (C.c_int, [_P, C.POINTER(CircuitInfo)]),
     "msc_circuit_expected": (C.c_int, [_P, _P]),

@@ -63,6 +63,7 @@ struct msc_ctx {
     hipGraphExec_t lx_exec = nullptr;
     std::string lx_key;
     msc_engine_stats lx_stats{}; // the engine in the last shot run
+    msc_shot_stats shot_stats{}; // the kernel that took its shots
     hipEvent_t lxev[6] = {};     // phase boundaries of an engine round
 };
 
@@ -148,6 +149,12 @@ extern "C" void msc_ctx_destroy(msc_ctx* ctx) {
 extern "C" int msc_ctx_engine_stats(msc_ctx* ctx, msc_engine_stats* out) {
     if (!ctx || !out) return set_error(MSC_E_INVALID, "null argument");
     *out = ctx->lx_stats;
+    return MSC_OK;
+}
+
+extern "C" int msc_ctx_shot_stats(msc_ctx* ctx, msc_shot_stats* out) {
+    if (!ctx || !out) return set_error(MSC_E_INVALID, "null argument");
+    *out = ctx->shot_stats;
     return MSC_OK;
 }
 
@@ -596,8 +603,16 @@ static int enqueue_wave(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, i
                            nullptr, 0, nullptr, nullptr, surv, a.retry_list);
         if (rc) return rc;
     }
+    // (after a rerun, which leaves its own)
     ctx->lx_stats.wave_slots = cfg.fast_wide ? 0 : slots;
     ctx->lx_stats.wave_retries = cfg.fast_wide ? 0 : n_retry;
+    ctx->shot_stats.kernel = !fast ? MSC_SHOT_KERNEL_WAVE
+                             : cw <= kFastWaveBond ? MSC_SHOT_KERNEL_FAST_WAVE
+                             : cw <= kFastMidBond  ? MSC_SHOT_KERNEL_FAST_MID
+                                                   : MSC_SHOT_KERNEL_FAST_GROUP;
+    ctx->shot_stats.slot_chi = cw;
+    ctx->shot_stats.slots = slots;
+    ctx->shot_stats.retries = n_retry;
     return MSC_OK;
 }
 
@@ -656,6 +671,7 @@ static int enqueue_shots(msc_ctx* ctx, const msc_circuit* c, const RunCfg& cfg, 
     a.scratch = static_cast<double*>(scratch);
     a.scratch_stride = L.scratch;
     ctx->lx_stats = msc_engine_stats{};
+    ctx->shot_stats = msc_shot_stats{MSC_SHOT_KERNEL_WORKGROUP, chi_max, n_slots, 0};
     void *dstate = nullptr, *dcount = nullptr, *dlist = nullptr, *dflops = nullptr;
     if (engine) {
         if ((rc = ctx_buf(ctx, "lx_state", static_cast<size_t>(n_slots) * sizeof(ShotState), &dstate))) return rc;
