@@ -165,7 +165,9 @@ typedef struct {
                              32 cl cm cr (contraction) + 32 cl^2 cr (Gram)
                              + 32 r cl cr (projection) + 104 cl^3 (eigen-
                              solve) with cl, cm, cr the bonds around the two
-                             sites and r the new bond                      */
+                             sites and r the new bond: a general update's
+                             count in every kernel, also where one rotation
+                             per pair takes the place of the last two terms */
     int64_t sweeps;       /* Jacobi sweeps summed over the shot's SVDs       */
 } msc_shot_result;
 

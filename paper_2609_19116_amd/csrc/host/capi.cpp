@@ -1062,9 +1062,10 @@ static int sim_cfg(const msc_sim_opts* o, const msc_circuit* c, RunCfg* cfg) {
              fast_path(c, o->chi_max) && c->noiseless.chi_peak <= kFastGroupBond) {
         // wider circuits: the matrix-core kernels of the next caps (49 qubits
         // on the snake layout, bond 32, 20000 shots: 79.7 ms in the workgroup
-        // kernel, 38.6 here; 256 shots of the 81-qubit patch, bond 64: 1159 ms
-        // and 211), unless the caller sets the workgroup kernel's width or the
-        // engine's
+        // kernel, 38.6 here; 81-qubit patch, bond 64: 256 survivors 998 ms and
+        // 177, 1024 shots from their start 3285 and 888; 49 qubits on the
+        // rainbow layout, bond 128: 1251 and 205, 5236 and 954), unless the
+        // caller sets the workgroup kernel's width or the engine's
         wc = c->noiseless.chi_peak <= kFastMidBond ? kFastMidBond : kFastGroupBond;
         cfg->fast_wide = true;
     }

@@ -1,5 +1,13 @@
-// One-wavefront shot kernel on the matrix cores: one shot per wavefront, four
-// per workgroup, for slots of bond cap at most 16.
+// Shot kernels on the matrix cores, by the bond cap of their slots:
+//   mps_fast_wave_kernel    at most 16: one shot per wavefront, four per
+//                           workgroup, three workgroups per CU;
+//   mps_fast_mid_kernel     at most 32: one shot per wavefront, seven per
+//                           workgroup and CU;
+//   mps_fast_group_kernel   at most 128: one shot per workgroup of eight
+//                           wavefronts and CU.  Wavefront 0 leads: it runs the
+//                           op stream and every op of bonds up to 16 alone and
+//                           hands the wider two-site ops to the team (wide,
+//                           follow).
 //
 // Same shot loop, ops and results as the wavefront kernel of mps.hip.  What
 // bounded that kernel was instruction issue and LDS traffic, not arithmetic:
@@ -171,6 +179,13 @@ __device__ __forceinline__ Kept wave_select(LW* L, double tau2, int capb,
     return k;
 }
 
+// The flops that the records count for an update (the contraction, the Gram
+// matrix, a projection and an eigen-decomposition at its shapes) are those of a
+// general factorisation, the unit in which all shot kernels count; the closed
+// form below needs neither of the last two, two thirds of the count at equal
+// bonds, and a wide centre move that counts as an update computes the Gram
+// matrix alone.
+//
 // Two-site update (as twosite_update) of sites whose theta has at most
 // 16 NVT vectors of at most 32 elements; the vectors live at V (LDS, or the
 // slot's scratch for 32 vectors of more than 16), vector v's real part at v ld
@@ -1332,7 +1347,11 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LW* L, const LTables*
     };
     const auto chi = [&](int k) { return uni(L->chi[k]); };
     const int lane0 = lane == 0;
-    // hands a wide op to the team
+    // Hands a wide op to the team.  The followers read the command and, in
+    // wide_op, the bonds after the barrier here and before the op's first one,
+    // so every wide op passes at least one barrier of the whole workgroup on
+    // every path (also where it returns early) and all wavefronts return from
+    // it alike; only then may the leader write a bond or the next command.
     const auto wide = [&](int kind, int a, int b, int gate_id) {
         if constexpr (NWT > 1) {
             if (lane0) {
@@ -1747,7 +1766,9 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LW* L, const LTables*
 }
 
 // The other wavefronts of a team: they join every wide op until the leader
-// has no shots left.
+// has no shots left (the barriers pair with wide() and those inside the op; a
+// wide op that some wavefront left without passing its barriers would hang the
+// workgroup or let the leader overwrite a command still to be read).
 template <typename T, int NWT, typename LW>
 __device__ __forceinline__ void follow(const MpsArgs& P, LW* L, const LTables* tab, int team) {
     typedef __attribute__((address_space(1))) T gT;

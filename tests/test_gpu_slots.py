@@ -101,6 +101,10 @@ def test_stats_name_the_kernel(ctx, name, kernel, slot):
     # a kernel that ran nothing would still have left its name
     for r in (res, alone):
         assert np.all(r["status"] & (msc.SHOT_DONE | msc.SHOT_REJECTED))
+    # gauge-independent counts (controlled-S circuits: their updates follow the
+    # basis of equal singular values, here that of one and the same sweep)
+    for f in ("chi_peak", "n2q", "flops", "status", "rejected_at", "fail"):
+        assert np.array_equal(res[f], alone[f]), f
 
 
 @pytest.mark.parametrize("precision", [MSC_FP64, MSC_FP32])
