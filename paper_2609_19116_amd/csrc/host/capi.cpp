@@ -246,12 +246,13 @@ static void free_device(msc_circuit* c) {
     free_camps_prefix(c->camps_prefix);
     if (c->dev < 0) return;
     (void)hipSetDevice(c->dev);
-    for (void** p : {&c->d_ops, &c->d_g1, &c->d_g4, &c->d_sig, &c->d_sig_off, &c->d_hash, &c->d_expected, &c->d_kind,
+    for (void** p : {&c->d_ops, &c->d_g1, &c->d_g4, &c->d_sig, &c->d_sig_off, &c->d_expected, &c->d_kind,
                      &c->d_segm, &c->d_camps_ops, &c->d_chan_q, &c->d_site_of, &c->d_dmat,
                      &c->d_dtab}) {
         if (*p) (void)hipFree(*p);
         *p = nullptr;
     }
+    c->d_hash = nullptr;      // (part of d_sig)
     c->dev = -1;
 }
 
@@ -259,6 +260,11 @@ extern "C" void msc_circuit_free(msc_circuit* c) {
     if (!c) return;
     free_device(c);
     delete c;
+}
+
+// Pauli codes of a channel (code 0: no fault).
+static int code_count(int kind) {
+    return kind == CH_DEP1 ? 4 : kind == CH_DEP2 ? 16 : kind == CH_XERR ? 2 : 64;
 }
 
 static int upload(msc_ctx* ctx, msc_circuit* c) {
@@ -283,36 +289,44 @@ static int upload(msc_ctx* ctx, msc_circuit* c) {
     {
         const int W = c->words;
         std::vector<int32_t> soff(std::max(1, c->n_channels));
+        c->hash_shift = 4;
+        size_t n_codes = 0;
+        for (int32_t k : c->chan_kind) {
+            if (n_codes >= (size_t(1) << 29))
+                return set_error(MSC_E_INVALID, "screen table above 2^29 entries");
+            if (k == CH_DEP3) c->hash_shift = 6;
+            n_codes += code_count(k);
+        }
+        const size_t entries = static_cast<size_t>(c->n_channels) << c->hash_shift;
+        const bool hashed = entries > 0 && entries <= kMaxHashEntries;
         std::vector<uint64_t> comb;
+        comb.reserve(n_codes * W + (hashed ? entries : 0));
+        comb.resize(n_codes * W);
+        size_t entry = 0;
         for (int ch = 0; ch < c->n_channels; ++ch) {
             const int k = c->chan_kind[ch];
-            const int codes = k == CH_DEP1 ? 4 : k == CH_DEP2 ? 16 : k == CH_XERR ? 2 : 64;
+            const int codes = code_count(k);
             // entry index of the channel's code 0, shifted, with its kind
             // in the low two bits: the screen reads both with one load
-            const size_t entry = comb.size() / std::max(1, W);
-            if (entry >= (size_t(1) << 29))
-                return set_error(MSC_E_INVALID, "screen table above 2^29 entries");
             soff[ch] = static_cast<int32_t>(entry << 2) | k;
-            for (int p = 0; p < codes; ++p)
-                for (int w = 0; w < W; ++w) {
-                    uint64_t x = 0;
-                    for (int b = 0; b < kFaultComponents; ++b)
-                        if ((p >> b) & 1)
-                            x ^= c->sig[(static_cast<size_t>(ch) * kFaultComponents + b) * W + w];
-                    comb.push_back(x);
-                }
+            // a code's signature: that of the code without its lowest
+            // component, and that component's
+            uint64_t* row = comb.data() + entry * W;
+            const uint64_t* sig = &c->sig[static_cast<size_t>(ch) * kFaultComponents * W];
+            for (int p = 1; p < codes; ++p)
+                for (int w = 0; w < W; ++w)
+                    row[p * W + w] = row[(p & (p - 1)) * W + w] ^ sig[__builtin_ctz(p) * W + w];
+            entry += codes;
         }
-        if ((rc = put(&c->d_sig, comb.data(), comb.size() * sizeof(uint64_t)))) return rc;
-        if ((rc = put(&c->d_sig_off, soff.data(), soff.size() * sizeof(int32_t)))) return rc;
-        // its first look: per (channel, code) a linear hash of the signature,
-        // the XOR of a fixed random 63-bit word per signature bit, at a fixed
-        // stride; the top bit marks codes the channel does not have
-        c->hash_shift = 4;
-        for (int32_t k : c->chan_kind)
-            if (k == CH_DEP3) c->hash_shift = 6;
-        const size_t entries = static_cast<size_t>(c->n_channels) << c->hash_shift;
-        if (entries <= kMaxHashEntries) {
-            std::vector<uint64_t> word(static_cast<size_t>(64) * W), hash(entries, kHashInvalid);
+        // its first look, behind the table in the same allocation: per (channel,
+        // code) a linear hash of the signature, the XOR of a fixed random 63-bit
+        // word per signature bit, at a fixed stride; the top bit marks codes the
+        // channel does not have
+        const size_t n_sig = comb.size();
+        if (hashed) {
+            comb.resize(n_sig + entries, kHashInvalid);
+            uint64_t* hash = comb.data() + n_sig;
+            std::vector<uint64_t> word(static_cast<size_t>(64) * W);
             uint64_t st = 0x7363726565ull;
             for (uint64_t& x : word) {      // SplitMix64
                 uint64_t z = (st += 0x9E3779B97F4A7C15ull);
@@ -320,20 +334,23 @@ static int upload(msc_ctx* ctx, msc_circuit* c) {
                 z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
                 x = (z ^ (z >> 31)) & ~kHashInvalid;
             }
-            for (int ch = 0; ch < c->n_channels; ++ch) {
-                const size_t e0 = static_cast<size_t>(soff[ch] >> 2);
-                const size_t e1 = ch + 1 < c->n_channels ? static_cast<size_t>(soff[ch + 1] >> 2)
-                                                         : comb.size() / std::max(1, W);
-                for (size_t p = 1; p < e1 - e0; ++p) {
-                    uint64_t h = 0;
+            for (int ch = 0; ch < c->n_channels; ++ch, hash += size_t(1) << c->hash_shift) {
+                uint64_t part[kFaultComponents];
+                const uint64_t* sig = &c->sig[static_cast<size_t>(ch) * kFaultComponents * W];
+                const int codes = code_count(c->chan_kind[ch]);
+                for (int b = 0; (1 << b) < codes; ++b) {
+                    part[b] = 0;
                     for (int w = 0; w < W; ++w)
-                        for (uint64_t m = comb[(e0 + p) * W + w]; m; m &= m - 1)
-                            h ^= word[static_cast<size_t>(64) * w + __builtin_ctzll(m)];
-                    hash[(static_cast<size_t>(ch) << c->hash_shift) + p] = h;
+                        for (uint64_t m = sig[static_cast<size_t>(b) * W + w]; m; m &= m - 1)
+                            part[b] ^= word[static_cast<size_t>(64) * w + __builtin_ctzll(m)];
                 }
+                for (int p = 1; p < codes; ++p)
+                    hash[p] = ((p & (p - 1)) ? hash[p & (p - 1)] : 0) ^ part[__builtin_ctz(p)];
             }
-            if ((rc = put(&c->d_hash, hash.data(), hash.size() * sizeof(uint64_t)))) return rc;
         }
+        if ((rc = put(&c->d_sig, comb.data(), comb.size() * sizeof(uint64_t)))) return rc;
+        if (hashed) c->d_hash = static_cast<uint64_t*>(c->d_sig) + n_sig;
+        if ((rc = put(&c->d_sig_off, soff.data(), soff.size() * sizeof(int32_t)))) return rc;
     }
     if ((rc = put(&c->d_expected, c->expected.data(), c->expected.size()))) return rc;
     std::vector<uint8_t> kind(c->chan_kind.begin(), c->chan_kind.end());

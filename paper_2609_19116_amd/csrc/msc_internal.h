@@ -151,7 +151,8 @@ struct msc_circuit {
     void* d_g4 = nullptr;
     void* d_sig = nullptr;               // uint64 [codes of all channels][words]
     void* d_sig_off = nullptr;           // int32 first code entry per channel
-    void* d_hash = nullptr;              // uint64 [n_channels << hash_shift], null if too large
+    void* d_hash = nullptr;              // uint64 [n_channels << hash_shift] behind d_sig, null
+                                         // if too large
     int hash_shift = 4;
     void* d_expected = nullptr;
     void* d_kind = nullptr;              // uint8 ChanKind per channel
