@@ -279,9 +279,10 @@ def main() -> int:
     n2q = [st["n2q"] for st in sts]
     chi_peak = max(st["chi_peak"] for st in sts)
     # roofline of the shot kernel: algorithmic flops of a launch (the
-    # library's per-update count at the realised shapes: contraction, Gram,
-    # projection, eigensolve) over the launch's
-    # duration (HIP events on the step's stream around the shot kernel).
+    # library's per-update count at the realised shapes of a general update:
+    # contraction, Gram, projection, eigensolve; the matrix-core kernels need
+    # the last two for next to no update, so the operations executed are given
+    # beside it, from the counters) over the launch's duration (HIP events on the step's stream around the shot kernel).
     # With one step in flight the launches do not overlap, so this is the
     # rate the kernel trace of the same command gives per launch.
     achieved = float(np.mean(flops)) / (float(np.mean(sim_ms)) * 1e-3) / 1e12
@@ -290,6 +291,8 @@ def main() -> int:
     shot_stats = ctxs[0].engine_stats()
     kernel_name = shot_kernel(shot_stats, args.lds_width)
     achieved_job = sum(flops) / wall / 1e12
+    mfma = measured_counter(layout_key, kernel_name, "valu_counters", "mfma_flops_per_launch")
+    mfma_tflops = mfma and mfma / (float(np.mean(sim_ms)) * 1e-3) / 1e12
     sweeps = sum(st["sweeps"] for st in sts)
     log(f"steps={args.steps} wall={wall:.3f}s value={value:.1f} shots/s survivors={n_surv} "
         f"sim_ms={sim_ms} screen_ms={screen_ms} sample_ms={sample_ms}")
@@ -354,10 +357,15 @@ def main() -> int:
                      "achieved_whole_job": achieved_job,
                      "frac_whole_job": achieved_job / PEAK_VALU,
                      "frac_of_fp32_packed_peak": achieved / PEAK_FP32,
+                     "mfma_executed": mfma_tflops,
+                     "mfma_executed_frac": mfma_tflops and mfma_tflops / PEAK_FP64,
                      "note": "vector-ALU peak without packed FP32 FMAs (256 CUs x 64 lanes x "
                              "2 flops x 2.4 GHz = 78.6 TFLOP/s, FP32 and FP64 alike), also the "
                              "FP64 matrix peak: contractions, Gram matrices and projections "
-                             "run on FP64 MFMA"},
+                             "run on FP64 MFMA.  achieved counts every update as a general "
+                             "factorisation, the records' unit; mfma_executed is what the "
+                             "counters saw on the matrix cores, tile padding included (null "
+                             "when the kernel changed since)"},
         "estimates": {str(p): e for p, e in zip([5e-4, 1e-3, 2e-3], est)},
         "intervals_r100": intervals,
         "order_search": order_info,
@@ -628,27 +636,31 @@ def shot_kernel(stats: dict, lds_width: int) -> str:
     return f"{name}<float{args.get(name, '')}>"
 
 
-def measured_traffic(layout_key: str, kernel_name: str):
-    """HBM bytes per shot-kernel launch from the committed counter summary of
+def measured_counter(layout_key: str, kernel_name: str, summary: str, key: str):
+    """A figure per shot-kernel launch from a committed counter summary of
     that kernel, or None when the kernel source or the layout changed since
     the counters were taken."""
     import hashlib
     base = kernel_name.split("<")[0]
     src = os.path.join(ROOT, "paper_2609_19116_amd", "csrc", "kernels",
                        "mps_fast.hip" if base.startswith("mps_fast") else "mps.hip")
-    summ = os.path.join(ROOT, "profiles", f"{base}_c3_hbm_counters.md")
+    summ = os.path.join(ROOT, "profiles", f"{base}_c3_{summary}.md")
     if not os.path.exists(summ):
         return None
     sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
     vals = {}
     for line in open(summ):
-        if ":" in line and line.split(":")[0] in ("traffic_bytes_per_launch", "kernel_sha256_16",
-                                                  "layout"):
+        if ":" in line and line.split(":")[0] in (key, "kernel_sha256_16", "layout"):
             k, v = line.split(":", 1)
             vals[k.strip()] = v.strip()
     if vals.get("kernel_sha256_16") != sha or vals.get("layout") != layout_key:
         return None
-    return float(vals["traffic_bytes_per_launch"])
+    return float(vals[key])
+
+
+def measured_traffic(layout_key: str, kernel_name: str):
+    """HBM bytes per shot-kernel launch."""
+    return measured_counter(layout_key, kernel_name, "hbm_counters", "traffic_bytes_per_launch")
 
 
 def contraction_lines(msc, ctx, torch) -> dict:
