@@ -40,6 +40,7 @@ constexpr int CT = 256;
 constexpr int K = kCampsK;
 constexpr int NR = 2 * kMaxSites;
 constexpr int kMaxSweeps = 60;
+constexpr int kPairSweeps = 30;    // two or three are usual
 constexpr double kOrtho = 1e-15;   // |x^H y| / (|x| |y|) of vectors that count as orthogonal
 // (sigma / sigma_max)^2 below which a column is the rounding of the others:
 // left as it is, so what it has along a kept column is lost with it.  It may
@@ -215,9 +216,9 @@ __device__ __forceinline__ void rr_pair(int i, int t, int m, int& p, int& q) {
 // In LDS, each sweep starts from the Gram matrix of the columns on FP64 MFMA:
 // pairs with |x^H y| <= kOrtho |x| |y| count as orthogonal, and columns at the
 // rounding of the largest one (kNoise2) as zero.  When every overlapping column
-// has exactly one mate, which is the usual case, all pairs rotate in one step;
-// else one round-robin sweep by wavefront 0, whose own sums decide: the columns
-// are orthogonal if it rotates nothing.  A round-robin sweep over 32 columns is
+// has exactly one mate, which is the usual case, all pairs rotate in one step
+// (in the first kPairSweeps sweeps); else one round-robin sweep by wavefront 0,
+// whose own sums decide: the columns are orthogonal if it rotates nothing.  A round-robin sweep over 32 columns is
 // 31 dependent steps and needed a second one to find nothing left: 256 49-qubit
 // shots (one shot's latency) 185 -> 121 ms.  The columns' squared norms are
 // left in J.nrm.
@@ -267,7 +268,8 @@ __device__ int jacobi_cols(const WV& w, int len, int nv, int* s_flag, LPair* J) 
             __syncthreads();
             const int over = J->over;
             if (over == 0) return sweep + 1;
-            if (over < 2) {
+            const bool pairs = over < 2 && sweep < kPairSweeps;
+            if (pairs) {
                 // the pairs of tile t by the lanes of their lower columns
                 const int t = nvt == 1 ? 0 : wid & 1, part = nvt == 1 ? wid : wid >> 1;
                 const int v = 16 * t + (tid & 15);
@@ -311,7 +313,7 @@ __device__ int jacobi_cols(const WV& w, int len, int nv, int* s_flag, LPair* J) 
                 if (tid == 0) J->rotated = r;
             }
             __syncthreads();
-            if (over >= 2 && !J->rotated) return sweep + 1;
+            if (!pairs && !J->rotated) return sweep + 1;
         }
         return -1;
     }
