@@ -47,10 +47,13 @@ namespace msc {
 namespace {
 
 // Truncation of the factorisations: keep sigma > tau * sigma_0, at most cap
-// vectors (the slot's bond cap, or chi_max below it).
+// vectors (the slot's bond cap, or chi_max below it).  Weight dropped with `full`
+// vectors kept counts as cut by the bond cap: chi_max, as in the workgroup
+// kernel, and in slots of cap 16 the slot's, as in the wavefront kernel.  (A
+// slot's own cap cuts nothing: a shot that needs more leaves it.)
 struct Trunc {
     double tau;
-    int chi_max, cap;
+    int chi_max, cap, full;
 };
 
 constexpr int kOps = 16;             // op descriptors held at a time
@@ -378,7 +381,7 @@ __device__ __forceinline__ bool wave_update(const Trunc P, LW* L, const LTables*
     if (kp.want > capb && capb < P.chi_max) return false;
     const int r = kp.r;
     acc.disc += kp.dropped;
-    if (kp.dropped > 1e-12 * total && r == capb) acc.status |= MSC_SHOT_CHI_CAP;
+    if (kp.dropped > 1e-12 * total && r == P.full) acc.status |= MSC_SHOT_CHI_CAP;
     const double renorm = rsqrt_nr(kp.kept);
     // isometric factor: A[k][e][c] = y_c[e] / sigma_c (dir 1), A[k+1][c][e]
     // (dir 0); centre factor: A[k+1][c][u] (dir 1), A[k][u][c] (dir 0)
@@ -505,7 +508,7 @@ __device__ __forceinline__ bool wave_move(const Trunc P, LW* L, SiteView<T> A,
     const Kept kp = wave_select<1>(L, tau2, capb, rank, isq, sq, nv);
     const int r = kp.r;
     acc.disc += kp.dropped;
-    if (kp.dropped > 1e-12 * total && r == capb) acc.status |= MSC_SHOT_CHI_CAP;
+    if (kp.dropped > 1e-12 * total && r == P.full) acc.status |= MSC_SHOT_CHI_CAP;
     const double renorm = rsqrt_nr(kp.kept);
     const int ue = dir ? r : 1, uv = dir ? 1 : len;
     const int me = dir ? 1 : r, mv = dir ? w : 1;
@@ -626,7 +629,7 @@ __device__ __forceinline__ bool wave_move8(const Trunc P, LW* L, SiteView<T> A, 
     const Kept kp = wave_select8(L, tau2, capb, rank, is, sc, nv);
     const int r = kp.r;
     acc.disc += kp.dropped;
-    if (kp.dropped > 1e-12 * total && r == capb) acc.status |= MSC_SHOT_CHI_CAP;
+    if (kp.dropped > 1e-12 * total && r == P.full) acc.status |= MSC_SHOT_CHI_CAP;
     sc *= rsqrt_nr(kp.kept);
     const int ue = dir ? r : 1, uv = dir ? 1 : len;
     const int me = dir ? 1 : r, mv = dir ? w : 1;
@@ -1044,7 +1047,7 @@ __device__ __forceinline__ WideOp team_update(const Trunc P, LW* L, const LTable
     const int r = kp.r;
     out.r = r;
     out.dropped = kp.dropped;
-    if (kp.dropped > 1e-12 * total && r == P.cap) out.status |= MSC_SHOT_CHI_CAP;
+    if (kp.dropped > 1e-12 * total && r == P.full) out.status |= MSC_SHOT_CHI_CAP;
     const double renorm = rsqrt_nr(kp.kept);
     gT* Ure = dir ? A.re : B.re;
     gT* Uim = dir ? A.im : B.im;
@@ -1154,7 +1157,7 @@ __device__ __forceinline__ WideOp team_move(const Trunc P, LW* L, SiteView<T> A,
     const int r = kp.r;
     out.r = r;
     out.dropped = kp.dropped;
-    if (kp.dropped > 1e-12 * total && r == P.cap) out.status |= MSC_SHOT_CHI_CAP;
+    if (kp.dropped > 1e-12 * total && r == P.full) out.status |= MSC_SHOT_CHI_CAP;
     const double renorm = rsqrt_nr(kp.kept);
     int moved = 0;
     for (int t = w; t < nvt; t += NWT)
@@ -1337,7 +1340,8 @@ __device__ __forceinline__ void run_wave(const MpsArgs& P, LW* L, const LTables*
     const int N = P.n_sites;
     gT* slot = to_glb(static_cast<T*>(P.arena) + (size_t)team * P.slot_stride);
     glbd* scr = to_glb(P.scratch + (size_t)team * P.scratch_stride);
-    const Trunc trunc{P.tau, P.chi_max, N > 1 ? min(P.chi_max, P.cap[1]) : 1};
+    const int cap = N > 1 ? min(P.chi_max, P.cap[1]) : 1;
+    const Trunc trunc{P.tau, P.chi_max, cap, NWT > 0 ? P.chi_max : cap};
     // (k is the same in every lane)
     const auto site = [&](int k) {
         SiteView<T> v;
@@ -1774,7 +1778,7 @@ __device__ __forceinline__ void follow(const MpsArgs& P, LW* L, const LTables* t
     typedef __attribute__((address_space(1))) T gT;
     gT* slot = to_glb(static_cast<T*>(P.arena) + (size_t)team * P.slot_stride);
     glbd* scr = to_glb(P.scratch + (size_t)team * P.scratch_stride);
-    const Trunc trunc{P.tau, P.chi_max, P.n_sites > 1 ? min(P.chi_max, P.cap[1]) : 1};
+    const Trunc trunc{P.tau, P.chi_max, P.n_sites > 1 ? min(P.chi_max, P.cap[1]) : 1, P.chi_max};
     for (;;) {
         __syncthreads();
         const int kind = uni(L->cmd[0]), a = uni(L->cmd[1]), b = uni(L->cmd[2]),

@@ -129,14 +129,15 @@ def test_group_kernel_matches_stored_oracle_values(ctx, name, chi, precision):
     assert not np.any(res["status"] & (msc.SHOT_CHI_CAP | msc.SHOT_NOCONV))
 
 
-def _nested_pairs(m):
+def _nested_pairs(m, depth=1):
     """m nested Bell pairs (bond 2^m between their halves) around two qubits
-    that CX entangles only in shots where T X T^dag or T Y T^dag, not the
-    identity, is left of a fault: those double the bond."""
+    that CX entangles only in shots where a fault between (T H)^depth and its
+    inverse leaves the first one off |0>: those double the bond."""
     n = 2 * m + 3
     a, b = m, m + 1
     pairs = [(i, n - 2 - i) for i in range(m)]
-    ops = [f"H {n - 1}", f"T {n - 1}", f"H {a}", f"T {a}", f"DEP1 {a}", f"TDG {a}", f"H {a}"]
+    ops = [f"H {n - 1}", f"T {n - 1}"] + [f"H {a}", f"T {a}"] * depth
+    ops += [f"DEP1 {a}"] + [f"TDG {a}", f"H {a}"] * depth
     for i, j in pairs:
         ops += [f"H {i}", f"CX {i} {j}"]
     ops += ["DEP1 0", f"CX {a} {b}", f"CX {a} {b}"]
@@ -144,6 +145,12 @@ def _nested_pairs(m):
         ops += [f"CX {i} {j}", f"H {i}"]
     return "\n".join([f"QUBITS {n}", f"SEED {n - 1}", "TARGET T"] + [f"R {q}" for q in range(n)]
                      + ops + [f"M {q}" for q in range(n - 1)]) + "\n"
+
+
+def _fault_list(faults):
+    off = np.concatenate([[0], np.cumsum([len(f) for f in faults])]).astype(np.int64)
+    return (off, np.array([k for f in faults for k in f], dtype=np.int32),
+            np.array([v for f in faults for v in f.values()], dtype=np.uint8))
 
 
 @pytest.mark.parametrize("precision", [MSC_FP64, MSC_FP32])
@@ -158,9 +165,7 @@ def test_shots_that_outgrow_their_slot(ctx, m, kernel, precision):
     c.calibrate(ctx)
     assert c.noiseless()["chi_peak"] == 2 ** m
     faults = [{}, {0: 1}, {0: 2}, {0: 3}, {1: 1}, {0: 1, 1: 3}, {0: 1}, {}]
-    off = np.concatenate([[0], np.cumsum([len(f) for f in faults])]).astype(np.int64)
-    ch = np.array([k for f in faults for k in f], dtype=np.int32)
-    pa = np.array([v for f in faults for v in f.values()], dtype=np.uint8)
+    off, ch, pa = _fault_list(faults)
     oc = parse(text)
     ref = np.array([(r.p_acc, r.infid, r.rejected_at) for r in (sv.run_shot(oc, f) for f in faults)])
     res = results_numpy(msc.simulate(ctx, c, *to_dev(off, ch, pa), precision=precision))
@@ -176,3 +181,27 @@ def test_shots_that_outgrow_their_slot(ctx, m, kernel, precision):
     assert ctx.engine_stats()["slot_retries"] == wide.sum()
     for f in FIELDS[:7]:
         assert np.array_equal(res[f], pf[f]), f
+
+
+@pytest.mark.parametrize("precision", [MSC_FP64, MSC_FP32])
+@pytest.mark.parametrize("m,kernel", [(5, "mps_fast_mid_kernel"), (7, "mps_fast_group_kernel")])
+def test_a_full_slot_is_no_bond_cap(ctx, m, kernel, precision):
+    # an X fault at depth 3 leaves amplitudes 0.146 and 0.989, Schmidt values in
+    # the ratio 0.148 on top of the pairs' equal ones: a threshold of 0.6 drops
+    # the smaller half, so the bond stays at the slots' cap, which cut nothing,
+    # and chi_max (256) is far away
+    c = msc.Circuit(_nested_pairs(m, depth=3))
+    say(f"full slot m={m} precision={precision}")
+    c.calibrate(ctx)
+    assert c.noiseless()["chi_peak"] == 2 ** m
+    dev = to_dev(*_fault_list([{}, {0: 1}, {0: 1, 1: 1}, {0: 1}]))
+    kw = dict(precision=precision, tau_trunc=0.6)
+    res = results_numpy(msc.simulate(ctx, c, *dev, **kw))
+    st = ctx.engine_stats()
+    assert (st["shot_kernel"], st["slot_chi"], st["slot_retries"]) == (kernel, 2 ** m, 0)
+    assert np.all(res["disc_weight"][1:] > 0.01) and np.all(res["chi_peak"] == 2 ** m)
+    assert not np.any(res["status"] & msc.SHOT_CHI_CAP)
+    ref = results_numpy(msc.simulate(ctx, c, *dev, wave_chi=-1, **kw))
+    for f in ("status", "chi_peak", "rejected_at", "fail", "n2q", "flops"):
+        assert np.array_equal(res[f], ref[f]), f
+    np.testing.assert_allclose(res["p_acc"], ref["p_acc"], rtol=2 * TOL[precision], atol=0)
